@@ -1239,142 +1239,200 @@ __global__ __launch_bounds__(kScanThreads) void asd_commit_kernel(
 // ------------------------------------------- LM-head-fused row pass (MFMA)
 //
 // z = H W^T for hidden states H [M, K] and output weights W [N, K] (both bf16,
-// K-contiguous), in binary32 on v_mfma_f32_32x32x16_bf16, reduced at once to
+// K-contiguous), in binary32 on v_mfma_f32_16x16x32_bf16, reduced at once to
 // each row's greatest (key, column) and the draft token's logit: the M x N
 // logits never reach memory.
 //
-// One workgroup of eight wavefronts per 256 x 256 output tile, two per SIMD:
-// wavefront w covers rows 128 (w / 4) .. + 128 and columns 64 (w % 4) .. + 64
-// as 4 x 2 MFMA tiles whose 128 accumulators per lane live in AGPRs.  With
-// two wavefronts per SIMD one issues while the other waits on its LDS reads or
-// at the barrier.  MFMA operand layout (lane l, element e): A row l % 32,
-// k = 8 (l / 32) + e; B column l % 32, same k; accumulator v of lane l is row
-// 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32.
+// One workgroup of eight wavefronts, two per SIMD, per tile of 256 weight rows
+// (vocabulary columns) x 32 kNr hidden-state rows.  The weights are the A
+// operand and the hidden states the B operand, so that a lane's accumulators
+// hold vocabulary columns of one hidden-state row and the ranking runs within
+// lanes.  Wavefront w covers columns 64 (w % 4) .. + 64 and rows
+// 16 kNr (w / 4) .. + 16 kNr as 4 x kNr MFMA tiles.  Operand layout (lane l,
+// element e): row l % 16 of the operand's 16, k = 8 (l / 16) + e; accumulator v
+// of lane l is column 4 (l / 16) + v, hidden-state row l % 16.
 //
-// K steps of 64 go through two LDS stages per operand, each [256 rows][128 B].
-// Global -> LDS copies are buffer loads that write LDS directly (no VGPR
-// staging); rows past M or N read as zero from the buffer resource.  The 16-B
-// chunk c of row r is stored at chunk c ^ lm_swz(r), which keeps both the
-// copies and the fragment reads free of bank conflicts.  The two stages are
-// distinct arrays so the compiler can tell that a copy into one stage does not
-// alias the fragment reads from the other.
+// K steps of 64 go through two LDS stages per operand, rows of 128 B.  Global
+// -> LDS copies are buffer loads that write LDS directly (no VGPR staging);
+// rows past M or N read as zero from the buffer resource.  The 16-B chunk c of
+// row r is stored at chunk c ^ lm_swz(r), which keeps both the copies and the
+// fragment reads free of bank conflicts.  The two stages are distinct arrays so
+// the compiler can tell that a copy into one stage does not alias the fragment
+// reads from the other.
 //
-// Software pipeline of one wavefront: the fragments of the next k-slice are
-// read while the current slice's 8 MFMAs issue (one LDS read per MFMA), and
-// the barrier that publishes the next stage sits before the last slice's
-// MFMAs, so the next stage's first reads and copies overlap them.
-constexpr int kLmTile = 256;
+// Software pipeline of one wavefront: the fragments of the next k-slice of 32
+// are read while the current slice's MFMAs issue.  The barrier that publishes
+// the next stage sits kJ0 row groups into the second slice's MFMAs, which cover
+// the last reads of the current stage; the next stage's first reads and the
+// copies into the freed stage overlap the rest.
+//
+// What bounds it is the chip's power.  4,352 rows, 151,936 columns, d = 5,120,
+// Gaussian data: 4.68-4.73 ms (1,430-1,446 TFLOP/s) at 1.6 GHz with the matrix
+// cores 85% busy; on data of ones the same kernel clocks 2.4 GHz.  So it is
+// built to spend little energy per flop: 16x16x32 MFMAs, which move half the
+// accumulator bytes of 32x32x16 (registers-only probe 1,955 against 1,725
+// TFLOP/s; this kernel's 32x32x16 predecessor took 5.08 ms on the same box),
+// operands repeated from one MFMA to the next, and an epilogue within lanes
+// (0.085 ms of the call; the predecessor's went through LDS, 0.15-0.2 ms).
+// With every copy an L2 hit it would take 4.32 ms, with no copies 3.77 ms.
+constexpr int kLmCols = 256;             // weight rows of a tile
 constexpr int kLmK = 64;
 constexpr int kLmThreads = 512;
 constexpr int kLmGroup = kLmheadGroup;   // weight tiles that share a hidden-state row tile
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
 #define ASD_LDS __attribute__((address_space(3)))
 
+constexpr int kWaitLds = 0xc07f;         // s_waitcnt lgkmcnt(0)
 constexpr int kRsrcWord3 = 0x00020000;   // raw buffer, 32-bit data format
 
-__device__ __forceinline__ int lm_swz(int r) { return (r & 7) ^ ((r >> 3) & 1); }
+// A 16-byte LDS read serves 16 lanes at a time: lanes 0-3, 12-15 and 20-27 of
+// each half wavefront, then the others.  Fragment reads put row l % 16 and
+// chunk l / 16 on lane l, two rows to the 256 B of all banks, so the rows of
+// one parity in such a group need distinct chunks: this gives them.
+__device__ __forceinline__ int lm_swz(int r) { return (r >> 1) & 7; }
 
-// One stage of one operand: tile rows 0..255, columns [k0b / 2, k0b / 2 + 64).
-// Row r of the tile starts at byte r * K2 of the buffer.  Wavefronts 0..3, one
-// per SIMD, copy; wavefront w copies the 1-KB blocks w, w + 4, ..., w + 28,
-// each 8 rows, and lane l fills 16-B position l % 8 of row l / 8 with k-chunk
-// (l % 8) ^ lm_swz(row).  The other wavefront of each SIMD issues none, so it
-// keeps the matrix core busy while its partner's copies are issued (measured
-// faster than all eight wavefronts copying four blocks each).
+// One stage of one operand: tile rows 0 .. 32 kBlocks - 1, columns [k0b / 2,
+// k0b / 2 + 64).  Row r of the tile starts at byte r * K2 of the buffer.
+// Wavefronts 0..3, one per SIMD, copy; wavefront w copies the 1-KB blocks w,
+// w + 4, ..., each 8 rows, and lane l fills 16-B position l % 8 of row l / 8
+// with k-chunk (l % 8) ^ lm_swz(row).  The other wavefront of each SIMD issues
+// none, so it keeps the matrix core busy while its partner's copies are issued
+// (measured faster than all eight wavefronts copying).
+template <int kBlocks>
 __device__ __forceinline__ void lm_copy_stage(rsrc_t rs, int K2, int k0b, int wave, int lane,
                                               __bf16* lds) {
     if (wave >= 4) return;
-    const int c = (lane & 7) ^ (lane >> 3) ^ (wave & 1);   // (lane & 7) ^ lm_swz(row)
-    const int voff = (wave * 8 + (lane >> 3)) * K2 + c * 16;
+    const int c = (lane & 7) ^ lm_swz((wave & 1) * 8 + (lane >> 3));
+    int voff = (wave * 8 + (lane >> 3)) * K2 + c * 16;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
+    for (int u = 0; u < kBlocks; ++u) {
         const int blk = u * 4 + wave;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (void ASD_LDS*)(lds + blk * 512), 16,
-                                                 voff + u * 32 * K2, k0b, 0, 0);
+        // The empty asm keeps the offsets in one register: hoisted out of the K
+        // loop they would take one register per block, and spill.
+        asm volatile("" : "+v"(voff));
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (void ASD_LDS*)(lds + blk * 512), 16, voff,
+                                                 k0b, 0, 0);
+        voff += 32 * K2;
     }
 }
-
-__device__ __forceinline__ void lm_frags(const __bf16* Ar, const __bf16* Br, int p,
-                                         bf16x8 (&a)[4], bf16x8 (&b)[2]) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) a[i] = *(const bf16x8*)(Ar + i * 32 * kLmK + p);
-#pragma unroll
-    for (int j = 0; j < 2; ++j) b[j] = *(const bf16x8*)(Br + j * 32 * kLmK + p);
-}
-
-__device__ __forceinline__ void lm_mfma8(const bf16x8 (&a)[4], const bf16x8 (&b)[2],
-                                         f32x16 (&acc)[4][2]) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-}
-
-// Interleave: one MFMA, then one LDS read, six times, then two MFMAs; the
-// variant for the stage boundary also spreads a copying wavefront's buffer
-// copies.
-#define LM_SCHED_READS()                                                     \
-    do {                                                                     \
-        _Pragma("unroll") for (int t_ = 0; t_ < 6; ++t_) {                   \
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);               \
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);               \
-        }                                                                    \
-        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);                   \
-    } while (0)
-#define LM_SCHED_READS_COPIES()                                              \
-    do {                                                                     \
-        _Pragma("unroll") for (int t_ = 0; t_ < 6; ++t_) {                   \
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);               \
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);               \
-            __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);               \
-        }                                                                    \
-        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);                   \
-        __builtin_amdgcn_sched_group_barrier(0x020, 2, 0);                   \
-    } while (0)
 
 struct LmCtx {
     rsrc_t rh, rw;
-    int K2, wave, lane, offA, offB, h, sw;
+    int K2, wave, lane;
+    int offA, offB;      // this lane's first fragment of slice 0 (elements)
 };
 
-// One K step on stage (Ac, Bc).  Slices 0..2 prefetch the next slice's
-// fragments.  Before slice 3 all wavefronts meet: the next stage (An, Bn) is
-// complete, (Ac, Bc) is no longer read, so the stage after next is copied into
-// it (k0b) and the next stage's first fragments are read.
-__device__ __forceinline__ void lm_step(const LmCtx& x, const __bf16* Ac, const __bf16* Bc,
-                                        const __bf16* An, const __bf16* Bn, int k0b,
-                                        bf16x8 (&fa)[2][4], bf16x8 (&fb)[2][2],
-                                        f32x16 (&acc)[4][2]) {
-#pragma unroll
-    for (int kk = 0; kk < 3; ++kk) {
-        lm_frags(Ac + x.offA, Bc + x.offB, ((2 * (kk + 1) + x.h) ^ x.sw) * 8, fa[(kk + 1) & 1],
-                 fb[(kk + 1) & 1]);
-        lm_mfma8(fa[kk & 1], fb[kk & 1], acc);
-        LM_SCHED_READS();
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this lane's copies of (An, Bn)
-    __syncthreads();
-    lm_copy_stage(x.rh, x.K2, k0b, x.wave, x.lane, (__bf16*)Ac);
-    lm_copy_stage(x.rw, x.K2, k0b, x.wave, x.lane, (__bf16*)Bc);
-    lm_frags(An + x.offA, Bn + x.offB, (x.h ^ x.sw) * 8, fa[0], fb[0]);
-    lm_mfma8(fa[1], fb[1], acc);
-    LM_SCHED_READS_COPIES();
+__device__ __forceinline__ bf16x8 lm_frag(const __bf16* stage, int off, int slice, int tile) {
+    return *(const bf16x8*)(stage + (off ^ (slice * 32)) + tile * 16 * kLmK);
 }
 
+// c += a b.  Written in asm so that an accumulator keeps its registers: the
+// compiler gives the builtin's result registers of its own, which the 256 of
+// two wavefronts per SIMD do not hold at 256-row tiles (it spilled in the K
+// loop).  The operands come from LDS reads, which the compiler waits for, and
+// an accumulator is next used at least three MFMAs later; who reads it
+// otherwise waits with lm_mfma_drain first.
+__device__ __forceinline__ void lm_mfma(const bf16x8& a, const bf16x8& b, f32x4& c) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
+}
+// Waits out the matrix core's write of the last results; the compiler reads
+// none of them before.
+template <int kNr>
+__device__ __forceinline__ void lm_mfma_drain(f32x4 (&acc)[4][kNr]) {
+    asm volatile("s_nop 15\n\ts_nop 15");
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < kNr; ++j) asm volatile("" : "+v"(acc[i][j]));
+}
+
+// MFMAs of row groups [kFrom, kTo) of one slice.  With `kRead`, the fragments
+// of slice `kSliceNext` of stage (Wn, Hn) replace the consumed ones: the weight
+// fragments go to `an`, and each row group's hidden-state fragment into the
+// register it was consumed from, right after its MFMAs.  The reads whose
+// registers are free from the start (the weights' and those of the row groups
+// before kFrom) are spread over the first row groups.  Odd row groups take the
+// weight fragments in reverse, so that consecutive MFMAs always share an operand
+// (registers-only probe, Gaussian operands: 2,050 against 2,020 TFLOP/s; the chip
+// is power limited and a repeated operand costs less).  The scheduling barriers
+// hold the compiler to this order: an earlier read of a fragment would need a
+// second register for it, and registers are what this kernel is short of; a
+// later one would be waited for.
+template <int kNr, int kFrom, int kTo, bool kRead, int kSliceNext>
+__device__ __forceinline__ void lm_slice(const LmCtx& x, const __bf16* Wn, const __bf16* Hn,
+                                         const bf16x8 (&a)[4], bf16x8 (&an)[4], bf16x8 (&b)[kNr],
+                                         f32x4 (&acc)[4][kNr]) {
+    constexpr int kFree = 4 + kFrom, kGroups = kTo - kFrom;
+    constexpr int kEven = kGroups > 0 ? (kFree + kGroups - 1) / kGroups : 0;
+    constexpr int kEach = kFrom > 0 && kEven < 2 ? 2 : kEven;   // the next slice's first operands early
+#pragma unroll
+    for (int j = kFrom; j < kTo; ++j) {
+        const int first = (j - kFrom) * kEach;
+        const int n = kFree - first < 0 ? 0 : kFree - first < kEach ? kFree - first : kEach;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int t = j & 1 ? 3 - i : i;
+            lm_mfma(a[t], b[j], acc[t][j]);
+            if constexpr (kRead) {
+#pragma unroll
+                for (int e = (i * n + 2) / 4; e < ((i + 1) * n + 2) / 4; ++e) {
+                    const int f = first + e;
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (f < 4) an[f < 4 ? f : 0] = lm_frag(Wn, x.offA, kSliceNext, f);
+                    else b[f < 4 ? 0 : f - 4] = lm_frag(Hn, x.offB, kSliceNext, f - 4);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        }
+        if constexpr (kRead) {
+            __builtin_amdgcn_sched_barrier(0);
+            b[j] = lm_frag(Hn, x.offB, kSliceNext, j);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+}
+
+// One K step on stage (Wc, Hc), whose slice 0 fragments are in (a0, b).  The
+// stage after next (k0b) is copied into (Wc, Hc) once it is no longer read.
+template <int kNr, int kJ0>
+__device__ __forceinline__ void lm_step(const LmCtx& x, __bf16* Wc, __bf16* Hc, const __bf16* Wn,
+                                        const __bf16* Hn, int k0b, bf16x8 (&a0)[4],
+                                        bf16x8 (&a1)[4], bf16x8 (&b)[kNr],
+                                        f32x4 (&acc)[4][kNr]) {
+    lm_slice<kNr, 0, kNr, true, 1>(x, Wc, Hc, a0, a1, b, acc);
+    __builtin_amdgcn_sched_barrier(0);
+    lm_slice<kNr, 0, kJ0, false, 0>(x, Wn, Hn, a1, a0, b, acc);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this lane's copies of (Wn, Hn)
+    __syncthreads();
+    lm_copy_stage<8>(x.rw, x.K2, k0b, x.wave, x.lane, Wc);
+    lm_copy_stage<kNr>(x.rh, x.K2, k0b, x.wave, x.lane, Hc);
+    lm_slice<kNr, kJ0, kNr, true, 0>(x, Wn, Hn, a1, a0, b, acc);
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// Maximum over the four lanes l, l ^ 16, l ^ 32, l ^ 48 (one hidden-state row).
+__device__ __forceinline__ int32_t lm_row_max(int32_t v) {
+    v = max(v, __shfl_xor(v, 16, 64));
+    return max(v, __shfl_xor(v, 32, 64));
+}
+
+template <int kNr>
 __global__ __launch_bounds__(kLmThreads) void asd_lmhead_kernel(
     const unsigned char* __restrict__ hidden, const unsigned char* __restrict__ weight,
-    int64_t M, int64_t N, int64_t K, int64_t tiles_m, int64_t tiles,
+    int64_t M, int64_t N, int64_t K, uint32_t tiles_m, uint32_t tiles,
     const int32_t* __restrict__ draft_tokens, unsigned long long* __restrict__ row_best,
     uint32_t* __restrict__ row_draft_bits) {
-    __shared__ __attribute__((aligned(1024))) __bf16 A0[kLmTile * kLmK];
-    __shared__ __attribute__((aligned(1024))) __bf16 B0[kLmTile * kLmK];
-    __shared__ __attribute__((aligned(1024))) __bf16 A1[kLmTile * kLmK];
-    __shared__ __attribute__((aligned(1024))) __bf16 B1[kLmTile * kLmK];
-    __shared__ int32_t s_draft[kLmTile];
+    constexpr int kRows = 32 * kNr;
+    constexpr int kJ0 = kNr >= 6 ? 2 : kNr >= 3 ? 1 : 0;
+    __shared__ __attribute__((aligned(1024))) __bf16 W0[kLmCols * kLmK];
+    __shared__ __attribute__((aligned(1024))) __bf16 H0[kRows * kLmK];
+    __shared__ __attribute__((aligned(1024))) __bf16 W1[kLmCols * kLmK];
+    __shared__ __attribute__((aligned(1024))) __bf16 H1[kRows * kLmK];
+    __shared__ int32_t s_draft[kRows];
+    __shared__ int32_t s_best[kRows];
 
     // XCD-aware order: workgroup i runs on XCD i % 8, and each XCD takes a run
     // of consecutive positions.  Positions run over groups of kLmGroup weight
@@ -1382,164 +1440,160 @@ __global__ __launch_bounds__(kLmThreads) void asd_lmhead_kernel(
     // the tiles of a group start together and read each hidden-state slice
     // once between them from L2, and a group of weight tiles serves the row
     // tiles that the XCD runs alongside it.
-    const int64_t per_xcd = gridDim.x / 8;
-    const int64_t linear = (int64_t)(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-    const int64_t tiles_n = (N + kLmTile - 1) / kLmTile;
-    const int64_t group = linear / (kLmGroup * tiles_m), within = linear % (kLmGroup * tiles_m);
-    const int64_t rt = within / kLmGroup, ct = group * kLmGroup + within % kLmGroup;
-    if (linear >= tiles || ct >= tiles_n) return;
-    const int64_t row0 = rt * kLmTile, col0 = ct * kLmTile;
+    const uint32_t linear = blockIdx.x % 8 * (gridDim.x / 8) + blockIdx.x / 8;
+    const uint32_t group = linear / (kLmGroup * tiles_m), within = linear % (kLmGroup * tiles_m);
+    // Divisions run on the vector unit: back to scalars, or each copy loops
+    // over the values its resource could have.
+    const int rt = __builtin_amdgcn_readfirstlane((int)(within / kLmGroup));
+    const int ct = __builtin_amdgcn_readfirstlane((int)(group * kLmGroup + within % kLmGroup));
+    if (linear >= tiles || (int64_t)ct * kLmCols >= N) return;
+    const int64_t row0 = (int64_t)rt * kRows, col0 = (int64_t)ct * kLmCols;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: scalar LDS targets
-    const int wm = wave >> 2, wn = wave & 3, h = lane >> 5;
-    if (tid < kLmTile) s_draft[tid] = row0 + tid < M ? draft_tokens[row0 + tid] : -1;
-
-    f32x16 acc[4][2];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = (f32x16)(0.0f);
+    const int wv = wave & 3, wr = wave >> 2;
 
     LmCtx x;
     x.K2 = (int)(K * 2);
     x.rh = __builtin_amdgcn_make_buffer_rsrc((void*)(hidden + row0 * x.K2), (short)0,
-                                             (int)(min((int64_t)kLmTile, M - row0) * x.K2),
+                                             (int)(min((int64_t)kRows, M - row0) * x.K2),
                                              kRsrcWord3);
     x.rw = __builtin_amdgcn_make_buffer_rsrc((void*)(weight + col0 * x.K2), (short)0,
-                                             (int)(min((int64_t)kLmTile, N - col0) * x.K2),
+                                             (int)(min((int64_t)kLmCols, N - col0) * x.K2),
                                              kRsrcWord3);
     x.wave = wave;
     x.lane = lane;
-    x.h = h;
-    x.sw = lm_swz(lane & 31);
-    x.offA = (wm * 128 + (lane & 31)) * kLmK;
-    x.offB = (wn * 64 + (lane & 31)) * kLmK;
+    const int chunk = (lane >> 4) ^ lm_swz(lane & 15);
+    x.offA = (wv * 64 + (lane & 15)) * kLmK + chunk * 8;
+    x.offB = (wr * 16 * kNr + (lane & 15)) * kLmK + chunk * 8;
 
     // K / 64 is even.  Copies past the last stage are clamped to it: they
     // refill a stage that is no longer read, and the fragments read after the
     // last stage are never used.
-    const int64_t KT = K / kLmK;
-    bf16x8 fa[2][4], fb[2][2];
-    lm_copy_stage(x.rh, x.K2, 0, wave, lane, A0);
-    lm_copy_stage(x.rw, x.K2, 0, wave, lane, B0);
+    const int KT = (int)(K / kLmK);
+    lm_copy_stage<8>(x.rw, x.K2, 0, wave, lane, W0);
+    lm_copy_stage<kNr>(x.rh, x.K2, 0, wave, lane, H0);
+    // Each row's draft token and its greatest key so far over all tiles.  The
+    // key may be stale by the time it is used; it only grows, so a stale one
+    // costs an atomic that changes nothing.
+    if (tid < kRows) {
+        const bool have = row0 + tid < M;
+        s_draft[tid] = have ? draft_tokens[row0 + tid] : -1;
+        s_best[tid] = have ? packed_key(__hip_atomic_load(row_best + row0 + tid, __ATOMIC_RELAXED,
+                                                          __HIP_MEMORY_SCOPE_AGENT))
+                           : 0x7fffffff;
+    }
+    f32x4 acc[4][kNr];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < kNr; ++j) acc[i][j] = (f32x4)(0.0f);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    lm_copy_stage(x.rh, x.K2, 2 * kLmK, wave, lane, A1);
-    lm_copy_stage(x.rw, x.K2, 2 * kLmK, wave, lane, B1);
-    lm_frags(A0 + x.offA, B0 + x.offB, (h ^ x.sw) * 8, fa[0], fb[0]);
-    for (int64_t s = 0; s < KT; s += 2) {
-        lm_step(x, A0, B0, A1, B1, (int)(min(s + 2, KT - 1) * 2 * kLmK), fa, fb, acc);
-        lm_step(x, A1, B1, A0, B0, (int)(min(s + 3, KT - 1) * 2 * kLmK), fa, fb, acc);
+    lm_copy_stage<8>(x.rw, x.K2, 2 * kLmK, wave, lane, W1);
+    lm_copy_stage<kNr>(x.rh, x.K2, 2 * kLmK, wave, lane, H1);
+    bf16x8 a0[4], a1[4], b[kNr];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a0[i] = lm_frag(W0, x.offA, 0, i);
+#pragma unroll
+    for (int j = 0; j < kNr; ++j) b[j] = lm_frag(H0, x.offB, 0, j);
+    lm_mfma_drain<kNr>(acc);                  // the zeros are written before an MFMA reads them
+    __builtin_amdgcn_s_waitcnt(kWaitLds);     // else the loop's first wait counts scalar loads too
+    for (int s = 0; s < KT; s += 2) {
+        lm_step<kNr, kJ0>(x, W0, H0, W1, H1, min(s + 2, KT - 1) * 2 * kLmK, a0, a1, b, acc);
+        lm_step<kNr, kJ0>(x, W1, H1, W0, H0, min(s + 3, KT - 1) * 2 * kLmK, a0, a1, b, acc);
     }
-
-    // ---- epilogue, through LDS (the stages are free now).  Four passes, one
-    // per 32-row slice i of each wavefront; pass i uses the stage pair i % 2,
-    // so one barrier per pass separates its stores from its scans.  E0 holds
-    // the slice rows of wm = 0, E1 those of wm = 1, each [32 rows][256
-    // columns] of logit bits, with the 16-B chunk c of row lr at chunk c ^
-    // ((c >> 4) & 3) ^ 4 (lr & 3) ^ 8 ((lr >> 2) & 1), which keeps the stores
-    // free of bank conflicts.  Eight threads then scan each of the 64 rows, 32
-    // columns each.
-    //
-    // A scan ranks raw patterns read as signed integers: per 16-B chunk a
-    // signed and an unsigned maximum, and the first chunk with the greatest
-    // signed maximum.  When that maximum is a number in [1, +inf] and the
-    // unsigned maximum shows no NaN with the sign bit set, it is the exact
-    // maximum of the 32 columns and the winning chunk's first element equal
-    // to it is their first maximum.  Otherwise (a NaN, no positive number, or
-    // columns past N, which take no part in the ranking) the thread ranks its
-    // columns again with exact keys.
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no copy outlives the main loop
-    int wbase[2];
+    lm_mfma_drain<kNr>(acc);
+
+    // ---- epilogue.  The four lanes l % 16 = r hold a row's 64 columns of this
+    // wavefront, 16 each, column order i, lane, v.  The greatest raw pattern
+    // read as a signed integer is the exact maximum when it is a number in
+    // [1, +inf] and the row holds no NaN (columns past N are +0 then, and
+    // cannot win).  Most rows end there: only a row whose maximum reaches its
+    // greatest key so far looks for the column and updates it.  A row group
+    // with a NaN or a row with no positive number ranks with exact keys.
+    const int64_t wcol0 = col0 + wv * 64;
+    int le = (int)threadIdx.x & 63;
+    asm volatile("" : "+v"(le));
+    const int lr = le & 15, lq = le >> 4;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int col = wn * 64 + j * 32 + (lane & 31);
-        const int cl = col >> 2;
-        wbase[j] = 4 * 256 * h + ((cl ^ ((cl >> 4) & 3) ^ (h << 3)) << 2) + (col & 3);
-    }
-    const int rr = tid >> 3, q = tid & 7;                 // scan: slice row, column eighth
-    const int lrr = rr & 31;
-    const int xr = ((lrr & 3) << 2) ^ (((lrr >> 2) & 1) << 3);
-    const int64_t qcol0 = col0 + q * 32;                  // first column of the eighth
-    const bool qfull = qcol0 + 32 <= N;
-    __syncthreads();
+    for (int j = 0; j < kNr; ++j) {
+        const int r = wr * 16 * kNr + j * 16 + lr;        // tile row
+        const bool have = row0 + r < M;
+        __builtin_amdgcn_sched_barrier(0);
+        uint32_t u[16];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        uint32_t* const E0 = (uint32_t*)((i & 1) ? A1 : A0);
-        uint32_t* const E1 = (uint32_t*)((i & 1) ? B1 : B0);
-        uint32_t* const Ew = wm ? E1 : E0;
+        for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
+            for (int v = 0; v < 4; ++v) {
                 // The element is copied out before its bits are taken: a bit
                 // cast of the vector element itself read element 0 for every v.
                 const float val = acc[i][j][v];
-                Ew[(wbase[j] ^ ((v & 3) << 4)) + 256 * (8 * (v >> 2) + (v & 3))] =
-                    __float_as_uint(val);
+                u[4 * i + v] = __float_as_uint(val);
             }
-        __syncthreads();
-        const int r = (rr >> 5) * 128 + i * 32 + lrr;      // tile row
-        const uint32_t* const Er = (rr < 32 ? E0 : E1) + lrr * 256;
-        auto chunk = [&](int c) {                          // chunk c of this thread's eighth
-            const int cl = q * 8 + c;
-            return *(const uint4*)(Er + ((cl ^ ((cl >> 4) & 3) ^ xr) << 2));
-        };
-        unsigned long long best = 0;                       // ranks below every key
-        if (row0 + r < M) {
-            int32_t bm = (int32_t)0x80000000;
-            uint32_t um = 0;
-            int bch = 0;
+        int32_t sm = (int32_t)u[0];
+        uint32_t um = u[0];
 #pragma unroll
-            for (int c = 0; c < 8; ++c) {
-                const uint4 f = chunk(c);
-                const int32_t m = max(max((int32_t)f.x, (int32_t)f.y), max((int32_t)f.z, (int32_t)f.w));
-                um = max(um, max(max(f.x, f.y), max(f.z, f.w)));
-                if (m > bm) {                              // strict: first chunk on ties
-                    bm = m;
-                    bch = c;
-                }
-            }
-            int32_t bk;
-            int bc;
-            if (qfull && bm >= 1 && bm <= KeyTraits<4>::kInf && um <= KeyTraits<4>::kNegInfPattern) {
-                const uint4 f = chunk(bch);
-                const int e = (int32_t)f.x == bm ? 0 : (int32_t)f.y == bm ? 1 : (int32_t)f.z == bm ? 2 : 3;
-                bk = bm;                                   // a positive number's key is its pattern
-                bc = bch * 4 + e;
-            } else {
-                bk = (int32_t)0x80000000;
-                bc = 0;
-                for (int c = 0; c < 8; ++c) {
-                    const uint4 f = chunk(c);
-                    const uint32_t fv[4] = {f.x, f.y, f.z, f.w};
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int k = qcol0 + c * 4 + e < N ? f32_key(fv[e]) : (int32_t)0x80000000;
-                        if (k > bk) {                      // strict: lowest column on ties
-                            bk = k;
-                            bc = c * 4 + e;
-                        }
-                    }
-                }
-            }
-            best = pack_kc(bk, qcol0 + bc);
-            const int64_t xo = (int64_t)s_draft[r] - qcol0;
-            if (xo >= 0 && xo < 32 && qcol0 + xo < N) {
-                const uint4 f = chunk((int)xo >> 2);
-                const uint32_t fv[4] = {f.x, f.y, f.z, f.w};
-                row_draft_bits[row0 + r] = fv[(int)xo & 3];
-            }
+        for (int e = 1; e < 16; ++e) {
+            sm = max(sm, (int32_t)u[e]);
+            um = max(um, u[e]);
         }
-        // The eight threads of a row (lanes 8k .. 8k + 7) combine by DPP: the
-        // lane pairs and quad pairs of quad_perm, then the mirror within each
-        // eight-lane half row.
-        best = dpp_umax64<0xb1>(best);                     // quad_perm [1, 0, 3, 2]
-        best = dpp_umax64<0x4e>(best);                     // quad_perm [2, 3, 0, 1]
-        best = dpp_umax64<0x141>(best);                    // row_half_mirror
-        if (q == 0 && row0 + r < M) atomicMax(row_best + row0 + r, best);
+        const bool nan = um > KeyTraits<4>::kNegInfPattern || sm > KeyTraits<4>::kInf;
+        sm = lm_row_max(sm);
+        const int32_t best = s_best[r];
+        unsigned long long packed = 0;                    // ranks below every key
+        bool update = false;
+        if (__ballot(have && (nan || sm < 1)) != 0ull) {
+            int32_t bk = (int32_t)0x80000000;
+            int64_t bc = wcol0;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int64_t c = wcol0 + 16 * (e >> 2) + 4 * lq + (e & 3);
+                const int32_t k = c < N ? f32_key(u[e]) : (int32_t)0x80000000;
+                if (k > bk) {                             // strict: lowest column on ties
+                    bk = k;
+                    bc = c;
+                }
+            }
+            packed = pack_kc(bk, bc);
+            unsigned long long o = __shfl_xor(packed, 16, 64);
+            packed = o > packed ? o : packed;
+            o = __shfl_xor(packed, 32, 64);
+            packed = o > packed ? o : packed;
+            update = have && packed_key(packed) >= best;
+        } else if (__ballot(have && sm >= best) != 0ull) {
+            int32_t c = 64;
+#pragma unroll
+            for (int e = 15; e >= 0; --e)                 // the lane's first equal column
+                c = (int32_t)u[e] == sm ? 16 * (e >> 2) + 4 * lq + (e & 3) : c;
+            c = min(c, __shfl_xor(c, 16, 64));
+            c = min(c, __shfl_xor(c, 32, 64));
+            packed = pack_kc(sm, wcol0 + c);
+            update = have && sm >= best;
+        }
+        if (update && lq == 0) atomicMax(row_best + row0 + r, packed);
+        // The draft token's logit, where this lane holds its column.
+        const int64_t xo = (int64_t)s_draft[r] - wcol0;
+        const bool mine = have && xo >= 0 && xo < 64 && wcol0 + xo < N && (((int)xo >> 2) & 3) == lq;
+        if (__ballot(mine) != 0ull) {
+            const int e0 = ((int)xo >> 4) * 4 + ((int)xo & 3);
+            uint32_t z = u[0];
+#pragma unroll
+            for (int e = 1; e < 16; ++e) z = e == e0 ? u[e] : z;
+            if (mine) row_draft_bits[row0 + r] = z;
+        }
     }
+}
+
+template <int kNr>
+void launch_lmhead_tiles(int64_t grid, hipStream_t stream, const void* hidden, const void* weight,
+                         int64_t rows, int64_t vocab, int64_t d, int64_t tiles_m, int64_t tiles,
+                         const int32_t* draft_tokens, unsigned long long* best,
+                         uint32_t* draft_bits) {
+    asd_lmhead_kernel<kNr><<<(unsigned)grid, kLmThreads, 0, stream>>>(
+        (const unsigned char*)hidden, (const unsigned char*)weight, rows, vocab, d, (uint32_t)tiles_m,
+        (uint32_t)tiles, draft_tokens, best, draft_bits);
 }
 
 __global__ void asd_fill_u64_kernel(unsigned long long* p, int64_t n, unsigned long long v) {
@@ -1549,20 +1603,18 @@ __global__ void asd_fill_u64_kernel(unsigned long long* p, int64_t n, unsigned l
 
 // ------------------------------------------------------- matrix-core probe
 //
-// The matrix-core work of asd_lmhead_kernel with no memory traffic: a
-// workgroup of eight wavefronts, each wavefront issuing 32
-// v_mfma_f32_32x32x16_bf16 per K step of 64 into its 4 x 2 accumulator tiles,
-// as the LM-head kernel does, with operand fragments held in registers.  Each
-// thread reads six fragments once from the caller's buffer and forms four
-// fragment sets from them (the elements rotated within each fragment), which
-// the steps cycle through, so that the matrix cores see data of the caller's
-// distribution (the power a matrix core draws depends on its operands' bits).
-// Workgroup w reads the data of workgroup w % 64, which then stays in the
-// cache.  Run over as many workgroups and steps as an LM-head launch, its
-// duration is the practical matrix-core ceiling of that launch under the
-// chip's power limit.  Thread 0 of each workgroup writes the binary32 bits of
-// the sum of its accumulators.
-constexpr int kProbeSets = 4;
+// The matrix-core work of asd_lmhead_kernel's 256-row tiles with no memory
+// traffic: a workgroup of eight wavefronts, each wavefront issuing 64
+// v_mfma_f32_16x16x32_bf16 per K step of 64 into its 4 x 8 accumulator tiles,
+// with operand fragments held in registers.  Each thread reads six fragments
+// once from the caller's buffer and forms four sets from them (the elements
+// rotated within each fragment), two sets to a k-slice of 32, so that the
+// matrix cores see data of the caller's distribution (the power a matrix core
+// draws depends on its operands' bits).  Workgroup w reads the data of
+// workgroup w % 64, which then stays in the cache.  Run over as many workgroups
+// and steps as an LM-head launch, its duration is the practical matrix-core
+// ceiling of that launch under the chip's power limit.  Thread 0 of each
+// workgroup writes the binary32 bits of the sum of its accumulators.
 constexpr int kProbeVecs = 6;                  // 16-byte fragments read per thread
 
 template <int R>
@@ -1574,38 +1626,43 @@ __device__ __forceinline__ bf16x8 rotate_elements(bf16x8 v) {
 __global__ __launch_bounds__(kLmThreads) void asd_mfma_probe_kernel(
     const bf16x8* __restrict__ operands, int64_t vectors, int64_t steps,
     uint32_t* __restrict__ out) {
-    bf16x8 a[kProbeSets][4], b[kProbeSets][2];
+    bf16x8 a[2][4], b[2][8];
     const int64_t first = ((int64_t)(blockIdx.x % 64) * kLmThreads + threadIdx.x) * kProbeVecs;
-    bf16x8 f[kProbeVecs];
 #pragma unroll
-    for (int k = 0; k < kProbeVecs; ++k) f[k] = operands[(first + k) % vectors];
-#pragma unroll
-    for (int k = 0; k < 6; ++k) {
-        bf16x8* const dst0 = k < 4 ? &a[0][k] : &b[0][k - 4];
-        bf16x8* const dst1 = k < 4 ? &a[1][k] : &b[1][k - 4];
-        bf16x8* const dst2 = k < 4 ? &a[2][k] : &b[2][k - 4];
-        bf16x8* const dst3 = k < 4 ? &a[3][k] : &b[3][k - 4];
-        *dst0 = f[k];
-        *dst1 = rotate_elements<1>(f[k]);
-        *dst2 = rotate_elements<2>(f[k]);
-        *dst3 = rotate_elements<3>(f[k]);
+    for (int k = 0; k < kProbeVecs; ++k) {
+        const bf16x8 f = operands[(first + k) % vectors];
+        if (k < 4) {
+            a[0][k] = f;
+            a[1][k] = rotate_elements<2>(f);
+        } else {
+            b[0][k - 4] = f;
+            b[1][k - 4] = rotate_elements<2>(f);
+        }
+        b[0][2 + k] = rotate_elements<1>(f);
+        b[1][2 + k] = rotate_elements<3>(f);
     }
-    f32x16 acc[4][2];
+    f32x4 acc[4][8];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = (f32x16)(0.0f);
+        for (int j = 0; j < 8; ++j) acc[i][j] = (f32x4)(0.0f);
     for (int64_t s = 0; s < steps; ++s) {
 #pragma unroll
-        for (int t = 0; t < kProbeSets; ++t) lm_mfma8(a[t], b[t], acc);
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    acc[i][j] =
+                        __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[t][i], b[t][j], acc[i][j], 0, 0, 0);
     }
     float sum = 0.0f;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < 8; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
+            for (int v = 0; v < 4; ++v) {
                 const float x = acc[i][j][v];
                 sum += x;
             }
@@ -1778,14 +1835,18 @@ hipError_t launch_lmhead_verify(const void* hidden, const void* weight, int64_t 
     asd_fill_u64_kernel<<<(unsigned)((rows + 255) / 256), 256, 0, stream>>>(best, rows, 0ull);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
-    const int64_t tiles_m = (rows + kLmTile - 1) / kLmTile;
+    const int64_t tiles_m = lmhead_row_tiles(rows);
     // positions: row tiles x the weight tiles rounded up to whole groups
     const int64_t tiles =
-        tiles_m * kLmGroup * (((vocab + kLmTile - 1) / kLmTile + kLmGroup - 1) / kLmGroup);
+        tiles_m * kLmGroup * (((vocab + kLmCols - 1) / kLmCols + kLmGroup - 1) / kLmGroup);
     const int64_t grid = (tiles + 7) / 8 * 8;
-    asd_lmhead_kernel<<<(unsigned)grid, kLmThreads, 0, stream>>>(
-        (const unsigned char*)hidden, (const unsigned char*)weight, rows, vocab, d, tiles_m,
-        tiles, a.draft_tokens, best, draft_bits);
+    static decltype(&launch_lmhead_tiles<1>) const launch[8] = {
+        launch_lmhead_tiles<1>, launch_lmhead_tiles<2>, launch_lmhead_tiles<3>,
+        launch_lmhead_tiles<4>, launch_lmhead_tiles<5>, launch_lmhead_tiles<6>,
+        launch_lmhead_tiles<7>, launch_lmhead_tiles<8>};
+    const int64_t nr = ((rows + tiles_m - 1) / tiles_m + 31) / 32;
+    launch[nr - 1](grid, stream, hidden, weight, rows, vocab, d, tiles_m, tiles, a.draft_tokens,
+                   best, draft_bits);
     if ((err = hipGetLastError()) != hipSuccess) return err;
     ScanArgs A = scan_args(a, rows, vocab, 2);
     A.splits = 1;

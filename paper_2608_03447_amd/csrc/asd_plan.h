@@ -166,6 +166,7 @@ inline size_t lmhead_workspace_bytes(int64_t rows, int32_t num_requests) {
 // LM-head tiles are 256 x 256; grid positions run over whole groups of
 // kLmheadGroup weight tiles (the kernel's tile order).
 constexpr int kLmheadGroup = 4;
+inline int64_t lmhead_row_tiles(int64_t rows) { return (rows + 255) / 256; }
 hipError_t launch_lmhead_verify(const void* hidden, const void* weight, int64_t d,
                                 int64_t vocab, int64_t rows, const CallArgs& a, void* workspace,
                                 hipStream_t stream);

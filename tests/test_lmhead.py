@@ -84,6 +84,24 @@ def test_exact_regime_bit_exact(rows, vocab, d):
     assert not bad, "differs in %s: %s" % (bad, describe(g, r))
 
 
+@pytest.mark.parametrize("rows", [31, 32, 33, 64, 65, 96, 128, 129, 160, 192, 193, 224, 225, 256,
+                                  257, 289, 513])
+def test_row_tile_heights_bit_exact(rows):
+    """The height of a row tile follows the row count in steps of 32: one case
+    at each height and at the edges between them, exact regime, with a weight
+    tile that is partly past the vocabulary."""
+    from asd_gpu import describe, mismatches
+    rng = np.random.default_rng(rows)
+    hidden, weight, draft = _exact_inputs(rng, rows, 515, 256)
+    lens = [3] * (rows // 4) + [rows % 4 - 1] * (rows % 4 > 0)
+    budget = np.stack([rng.uniform(0, 6, len(lens)), np.zeros(len(lens))], axis=1)
+    print("case lmhead tile height rows %d" % rows, flush=True)
+    g = _run(hidden, weight, draft, lens, 1.0, 2, budget)
+    r = oracle.lmhead_verify(hidden, weight, draft, lens, 1.0, 2, budget)
+    bad = mismatches(g, r)
+    assert not bad, "differs in %s: %s" % (bad, describe(g, r))
+
+
 @pytest.mark.parametrize("rows,vocab,d", [(130, 1027, 128), (40, 5000, 256), (300, 640, 128)])
 def test_nonfinite_and_negative_rows_bit_exact(rows, vocab, d):
     """Rows that the epilogue cannot rank by raw patterns: every logit negative,
