@@ -562,6 +562,13 @@ asd_status asd_lmhead_verify(const void* hidden, const void* weight, int64_t d, 
     const int64_t tiles = ((total_rows + 255) / 256) * kLmheadGroup *
                           (((vocab + 255) / 256 + kLmheadGroup - 1) / kLmheadGroup);
     if (tiles >= ((int64_t)1 << 31) - 8) return ASD_EINVAL;
+    int device = 0, cus = 0;
+    if (hipGetDevice(&device) != hipSuccess) return ASD_EHIP;
+    {
+        std::lock_guard<std::mutex> lock(g_mutex);
+        st = cu_count(device, &cus);
+    }
+    if (st != ASD_OK) return st;
     hipStream_t s = (hipStream_t)stream;
     void* ws = nullptr;
     if ((st = library_workspace(s, lmhead_workspace_bytes(total_rows, num_requests), &ws)) !=
@@ -580,7 +587,7 @@ asd_status asd_lmhead_verify(const void* hidden, const void* weight, int64_t d, 
     a.out_next_token = out_next_token;
     a.out_argmax = out_argmax;
     a.out_regret = out_regret;
-    return launch_lmhead_verify(hidden, weight, d, vocab, total_rows, a, ws, s) == hipSuccess
+    return launch_lmhead_verify(hidden, weight, d, vocab, total_rows, a, ws, cus, s) == hipSuccess
                ? ASD_OK
                : ASD_EHIP;
 }

@@ -1285,6 +1285,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
 #define ASD_LDS __attribute__((address_space(3)))
 
+constexpr int kLmStreamMaxRows = 128;    // fewer rows stream the weights
 constexpr int kWaitLds = 0xc07f;         // s_waitcnt lgkmcnt(0)
 constexpr int kRsrcWord3 = 0x00020000;   // raw buffer, 32-bit data format
 
@@ -1419,6 +1420,85 @@ __device__ __forceinline__ int32_t lm_row_max(int32_t v) {
     return max(v, __shfl_xor(v, 32, 64));
 }
 
+// Ranks 16 hidden-state rows (one per lane l % 16, rows past M have `have`
+// unset) over 4 kElems columns: the four lanes of a row, lq = l / 16, hold
+// kElems logits each, element e at column wcol0 + 16 (e / 4) + 4 lq + e % 4.
+// The greatest raw pattern read as a signed integer is the exact maximum when
+// it is a number in [1, +inf] and the row holds no NaN (columns past N are +0
+// then, and cannot win).  Most rows end there: only a row whose maximum reaches
+// `best`, its greatest key when this tile started, looks for the column and
+// updates it (a stale `best` is lower, and costs an atomic that changes
+// nothing).  Rows with a NaN or no positive number rank with exact keys.  The
+// lane that holds the column of the row's draft token x writes its logit.
+template <int kElems>
+__device__ __forceinline__ unsigned long long lm_rank_rows(const uint32_t (&u)[kElems], int lq,
+                                                           int64_t wcol0, int64_t N, bool have,
+                                                           int32_t best) {
+    int32_t sm = (int32_t)u[0];
+    uint32_t um = u[0];
+#pragma unroll
+    for (int e = 1; e < kElems; ++e) {
+        sm = max(sm, (int32_t)u[e]);
+        um = max(um, u[e]);
+    }
+    const bool nan = um > KeyTraits<4>::kNegInfPattern || sm > KeyTraits<4>::kInf;
+    sm = lm_row_max(sm);
+    unsigned long long packed = 0;                    // ranks below every key
+    if (__ballot(have && (nan || sm < 1)) != 0ull) {
+        int32_t bk = (int32_t)0x80000000;
+        int64_t bc = wcol0;
+#pragma unroll
+        for (int e = 0; e < kElems; ++e) {
+            const int64_t c = wcol0 + 16 * (e >> 2) + 4 * lq + (e & 3);
+            const int32_t k = c < N ? f32_key(u[e]) : (int32_t)0x80000000;
+            if (k > bk) {                             // strict: lowest column on ties
+                bk = k;
+                bc = c;
+            }
+        }
+        packed = pack_kc(bk, bc);
+        unsigned long long o = __shfl_xor(packed, 16, 64);
+        packed = o > packed ? o : packed;
+        o = __shfl_xor(packed, 32, 64);
+        packed = o > packed ? o : packed;
+        if (packed_key(packed) < best) packed = 0;
+    } else if (__ballot(have && sm >= best) != 0ull) {
+        int32_t c = 4 * kElems;
+#pragma unroll
+        for (int e = kElems - 1; e >= 0; --e)         // the lane's first equal column
+            c = (int32_t)u[e] == sm ? 16 * (e >> 2) + 4 * lq + (e & 3) : c;
+        c = min(c, __shfl_xor(c, 16, 64));
+        c = min(c, __shfl_xor(c, 32, 64));
+        if (sm >= best) packed = pack_kc(sm, wcol0 + c);
+    }
+    return have ? packed : 0;
+}
+
+// The lane that holds the column of its row's draft token x (of the columns of
+// lm_rank_rows) writes its logit.
+template <int kElems>
+__device__ __forceinline__ void lm_draft_logit(const uint32_t (&u)[kElems], int lq, int64_t wcol0,
+                                               int64_t N, int64_t row, bool have, int32_t x,
+                                               uint32_t* row_draft_bits) {
+    const int64_t xo = (int64_t)x - wcol0;
+    const bool mine =
+        have && xo >= 0 && xo < 4 * kElems && (int64_t)x < N && (((int)xo >> 2) & 3) == lq;
+    if (__ballot(mine) != 0ull) {
+        const int e0 = ((int)xo >> 4) * 4 + ((int)xo & 3);
+        uint32_t z = 0;
+#pragma unroll
+        for (int e = 0; e < kElems; ++e) z |= e == e0 ? u[e] : 0u;   // no indexing: registers
+        if (mine) row_draft_bits[row] = z;
+    }
+}
+
+// A row's greatest key so far over all tiles, read past the caches that other
+// tiles' atomics do not pass.
+__device__ __forceinline__ int32_t lm_best_key(const unsigned long long* row_best, int64_t row) {
+    return packed_key(
+        __hip_atomic_load(row_best + row, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+
 template <int kNr>
 __global__ __launch_bounds__(kLmThreads) void asd_lmhead_kernel(
     const unsigned char* __restrict__ hidden, const unsigned char* __restrict__ weight,
@@ -1426,7 +1506,7 @@ __global__ __launch_bounds__(kLmThreads) void asd_lmhead_kernel(
     const int32_t* __restrict__ draft_tokens, unsigned long long* __restrict__ row_best,
     uint32_t* __restrict__ row_draft_bits) {
     constexpr int kRows = 32 * kNr;
-    constexpr int kJ0 = kNr >= 6 ? 2 : kNr >= 3 ? 1 : 0;
+    constexpr int kJ0 = kNr >= 6 ? 2 : 1;
     __shared__ __attribute__((aligned(1024))) __bf16 W0[kLmCols * kLmK];
     __shared__ __attribute__((aligned(1024))) __bf16 H0[kRows * kLmK];
     __shared__ __attribute__((aligned(1024))) __bf16 W1[kLmCols * kLmK];
@@ -1473,15 +1553,10 @@ __global__ __launch_bounds__(kLmThreads) void asd_lmhead_kernel(
     const int KT = (int)(K / kLmK);
     lm_copy_stage<8>(x.rw, x.K2, 0, wave, lane, W0);
     lm_copy_stage<kNr>(x.rh, x.K2, 0, wave, lane, H0);
-    // Each row's draft token and its greatest key so far over all tiles.  The
-    // key may be stale by the time it is used; it only grows, so a stale one
-    // costs an atomic that changes nothing.
-    if (tid < kRows) {
+    if (tid < kRows) {                        // each row's draft token and greatest key so far
         const bool have = row0 + tid < M;
         s_draft[tid] = have ? draft_tokens[row0 + tid] : -1;
-        s_best[tid] = have ? packed_key(__hip_atomic_load(row_best + row0 + tid, __ATOMIC_RELAXED,
-                                                          __HIP_MEMORY_SCOPE_AGENT))
-                           : 0x7fffffff;
+        s_best[tid] = have ? lm_best_key(row_best, row0 + tid) : 0x7fffffff;
     }
     f32x4 acc[4][kNr];
 #pragma unroll
@@ -1506,21 +1581,13 @@ __global__ __launch_bounds__(kLmThreads) void asd_lmhead_kernel(
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no copy outlives the main loop
     lm_mfma_drain<kNr>(acc);
 
-    // ---- epilogue.  The four lanes l % 16 = r hold a row's 64 columns of this
-    // wavefront, 16 each, column order i, lane, v.  The greatest raw pattern
-    // read as a signed integer is the exact maximum when it is a number in
-    // [1, +inf] and the row holds no NaN (columns past N are +0 then, and
-    // cannot win).  Most rows end there: only a row whose maximum reaches its
-    // greatest key so far looks for the column and updates it.  A row group
-    // with a NaN or a row with no positive number ranks with exact keys.
+    // ---- epilogue
     const int64_t wcol0 = col0 + wv * 64;
     int le = (int)threadIdx.x & 63;
-    asm volatile("" : "+v"(le));
-    const int lr = le & 15, lq = le >> 4;
+    asm volatile("" : "+v"(le));              // recomputed, not kept through the K loop
 #pragma unroll
     for (int j = 0; j < kNr; ++j) {
-        const int r = wr * 16 * kNr + j * 16 + lr;        // tile row
-        const bool have = row0 + r < M;
+        const int r = wr * 16 * kNr + j * 16 + (le & 15);        // tile row
         __builtin_amdgcn_sched_barrier(0);
         uint32_t u[16];
 #pragma unroll
@@ -1532,58 +1599,254 @@ __global__ __launch_bounds__(kLmThreads) void asd_lmhead_kernel(
                 const float val = acc[i][j][v];
                 u[4 * i + v] = __float_as_uint(val);
             }
-        int32_t sm = (int32_t)u[0];
-        uint32_t um = u[0];
+        const bool have = row0 + r < M;
+        const unsigned long long p = lm_rank_rows<16>(u, le >> 4, wcol0, N, have, s_best[r]);
+        if (p != 0 && le < 16) atomicMax(row_best + row0 + r, p);
+        lm_draft_logit<16>(u, le >> 4, wcol0, N, row0 + r, have, s_draft[r], row_draft_bits);
+    }
+}
+
+// ---- few rows: the weights' stream
+//
+// Up to 128 hidden-state rows.  The call is then bound by reading the weights
+// once, and the tile kernel above leaves most of the memory idle (one 32-KB
+// stage per CU in flight, a last round of tiles that is part full).  Here the
+// workgroups that the CUs hold at once take equal shares of the weight rows, in
+// tiles of 16 kVt kWaves, and stream them without a break: K steps of kK run
+// through a ring of kStages LDS stages, kStages - 1 of them in flight, across
+// the tiles of a share.  Wavefront w copies and multiplies the tile's weight
+// rows 16 kVt w .. against every hidden-state row (16 kRt at most), in the
+// operand layouts of the tile kernel, and keeps each row's greatest pair in
+// registers; the workgroup updates the rows once, at its end.
+//
+//  - The weights are read once: their copies are non-temporal (9 rows of the
+//    headline vocabulary, d = 5,120: 264 us cached, 238 us so).
+//  - Each copied row is at least a whole 128-B line per step.  With fragments
+//    loaded straight into registers (64 B of 16 rows per load) the same call
+//    took 293 us.
+//  - With kSpread, workgroups start their K loops at different steps: rows that
+//    are a multiple of 4 KB apart otherwise fall on few memory channels at a
+//    time (151,936 columns, 32 rows, d = 2,048: 124.5 us in step, 106.6 us so;
+//    d = 4,096: 202.6 and 197.9; d = 1,024, 2,560, 3,072, 5,120 and 7,168 within
+//    2% of each other).  A logit is then the sum of two chains, of every other
+//    k-slice, so that the changed order has less rounding and not more.
+//
+// 151,936 columns, d = 5,120, call times on one box against the tile kernels
+// that took these rows before: 9 rows 236 us (6.6 TB/s) against 425; 32 rows
+// 249 / 424; 64 rows 274 / 415; 128 rows 334 / 433.
+//
+// The copies are written in asm: they fill LDS and no registers, and the
+// compiler, which cannot tell a ring's stages apart, would wait for all of them
+// before any fragment read.  Each K step waits until at most the copies of the
+// later stages are outstanding (they complete in order), then meets the other
+// wavefronts: the step's stage is whole, and the stage before it is read out
+// and takes the next copies.  The wait states before a copy cover a resource
+// or LDS address that has just been written.
+template <bool kNonTemporal>
+__device__ __forceinline__ void lm_lds_copy(u32x4 rsrc, int voff, int k0b, uint32_t lds) {
+    if constexpr (kNonTemporal)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
+                     :
+                     : "s"(lds), "v"(voff), "s"(rsrc), "s"(k0b)
+                     : "memory");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                     :
+                     : "s"(lds), "v"(voff), "s"(rsrc), "s"(k0b)
+                     : "memory");
+}
+
+__device__ __forceinline__ void lm_lds_copy_dword(u32x4 rsrc, int voff, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dword %1, %2, 0 offen lds"
+                 :
+                 : "s"(lds), "v"(voff), "s"(rsrc)
+                 : "memory");
+}
+
+template <int kOutstanding>
+__device__ __forceinline__ void lm_stage_barrier() {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(kOutstanding) : "memory");
+}
+
+// Waits for the oldest stage with `later` whole stages (at most kMost) of kPer
+// copies per wavefront behind it.
+template <int kMost, int kPer>
+__device__ __forceinline__ void lm_stage_wait(int later) {
+    if constexpr (kMost == 0) {
+        lm_stage_barrier<0>();
+    } else {
+        if (later >= kMost) lm_stage_barrier<kMost * kPer>();
+        else lm_stage_wait<kMost - 1, kPer>(later);
+    }
+}
+
+__device__ __forceinline__ u32x4 lm_rsrc(const unsigned char* base, int bytes) {
+    const uint64_t p = (uint64_t)base;
+    u32x4 r;
+    r.x = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)p);
+    r.y = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(p >> 32) & 0xffffu));
+    r.z = (uint32_t)__builtin_amdgcn_readfirstlane(bytes);
+    r.w = (uint32_t)kRsrcWord3;
+    return r;
+}
+
+template <int kWaves, int kVt, int kRt, int kK, int kStages, bool kSpread>
+__global__ __launch_bounds__(64 * kWaves) void asd_lmhead_stream_kernel(
+    const unsigned char* __restrict__ hidden, const unsigned char* __restrict__ weight,
+    int32_t M, int64_t K, uint32_t share, uint32_t extra, const int32_t* __restrict__ draft_tokens,
+    unsigned long long* __restrict__ row_best, uint32_t* __restrict__ row_draft_bits) {
+    static_assert(kK == 64 || kK == 128, "rows of one or two cache lines");
+    constexpr int kCols = 16 * kVt * kWaves, kPitch = 2 * kK;
+    constexpr int kStageBytes = (kCols + 16 * kRt) * kPitch;
+    constexpr int kChains = kSpread ? 2 : 1;             // accumulators of one logit
+    constexpr int kDraftBytes = (16 * kRt + 63) / 64 * 256;
+    constexpr int kW = kVt * kK / 32, kH = kRt * kK / 32 / kWaves;   // blocks a wavefront copies
+    static_assert(kH * kWaves * 32 == kRt * kK && kStages >= 2, "every wavefront copies alike");
+    __shared__ __attribute__((aligned(1024))) unsigned char ring[kStages * kStageBytes + kDraftBytes];
+    const int32_t* const s_draft = (const int32_t*)(ring + kStages * kStageBytes);
+    const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, lq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int K2 = (int)(K * 2), KT = (int)(K / kK);
+    // This workgroup's weight rows, an equal share, in tiles of kCols.
+    const uint32_t bid = blockIdx.x;
+    const int64_t first = (int64_t)bid * share + min(bid, extra);
+    const int64_t end = first + share + (bid < extra);
+    const int steps = (int)((end - first + kCols - 1) / kCols) * KT;
+    const u32x4 rh = lm_rsrc(hidden, M * K2);
+    auto tile_rsrc = [&](int64_t col) {
+        return lm_rsrc(weight + col * K2, (int)(min((int64_t)kCols, end - col) * K2));
+    };
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(unsigned char ASD_LDS*)ring;
+
+    // 1-KB blocks of 512 / kK rows; the 16-B position p of row r holds k-chunk
+    // p ^ swz(r) (no bank conflicts in copies and fragment reads).
+    auto swz = [](int r) { return kK == 64 ? lm_swz(r & 15) : r & 15; };
+    constexpr int kLanes = kK / 8;                       // lanes, and 16-B chunks, of a row
+    auto lane_offset = [&](int block) {
+        const int row = block * (64 / kLanes) + lane / kLanes;
+        return row * K2 + ((lane % kLanes) ^ swz(row)) * 16;
+    };
+    int vw[kW], vh[kH];
 #pragma unroll
-        for (int e = 1; e < 16; ++e) {
-            sm = max(sm, (int32_t)u[e]);
-            um = max(um, u[e]);
+    for (int u = 0; u < kW; ++u) vw[u] = lane_offset(wave * kW + u);
+#pragma unroll
+    for (int u = 0; u < kH; ++u) vh[u] = lane_offset(wave * kH + u);
+    // The next step to copy: of tile `ccol`, byte `ck` of each row.
+    int64_t ccol = first;
+    u32x4 rw = tile_rsrc(ccol);
+    int ck = kSpread ? (int)(bid % (uint32_t)KT) * kPitch : 0, c_left = KT;
+    auto copy_next = [&](int slot) {
+        const uint32_t base = lds0 + slot * kStageBytes;
+#pragma unroll
+        for (int u = 0; u < kW; ++u) lm_lds_copy<true>(rw, vw[u], ck, base + (wave * kW + u) * 1024);
+#pragma unroll
+        for (int u = 0; u < kH; ++u)
+            lm_lds_copy<false>(rh, vh[u], ck, base + kCols * kPitch + (wave * kH + u) * 1024);
+        ck = ck + kPitch < K2 ? ck + kPitch : 0;
+        if (--c_left == 0) {
+            c_left = KT;
+            ccol += kCols;
+            if (ccol < end) rw = tile_rsrc(ccol);
         }
-        const bool nan = um > KeyTraits<4>::kNegInfPattern || sm > KeyTraits<4>::kInf;
-        sm = lm_row_max(sm);
-        const int32_t best = s_best[r];
-        unsigned long long packed = 0;                    // ranks below every key
-        bool update = false;
-        if (__ballot(have && (nan || sm < 1)) != 0ull) {
-            int32_t bk = (int32_t)0x80000000;
-            int64_t bc = wcol0;
+    };
+    // The draft tokens, by the oldest copies of all.
+    const u32x4 rd = lm_rsrc((const unsigned char*)draft_tokens, M * 4);
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int64_t c = wcol0 + 16 * (e >> 2) + 4 * lq + (e & 3);
-                const int32_t k = c < N ? f32_key(u[e]) : (int32_t)0x80000000;
-                if (k > bk) {                             // strict: lowest column on ties
-                    bk = k;
-                    bc = c;
-                }
+    for (int u = 0; u < (16 * kRt + 63) / 64; ++u)
+        lm_lds_copy_dword(rd, (u * 64 + lane) * 4, lds0 + kStages * kStageBytes + u * 256);
+    unsigned long long top[kRt];              // greatest (key, column) of this wavefront's columns
+#pragma unroll
+    for (int j = 0; j < kRt; ++j) top[j] = 0; // ranks below every key
+    for (int t = 0; t < kStages - 1 && t < steps; ++t) copy_next(t);
+    f32x4 acc[kChains][kVt][kRt];
+#pragma unroll
+    for (int c = 0; c < kChains; ++c)
+#pragma unroll
+        for (int i = 0; i < kVt; ++i)
+#pragma unroll
+            for (int j = 0; j < kRt; ++j) acc[c][i][j] = (f32x4)(0.0f);
+    const int offA = (wave * 16 * kVt + lr) * kPitch + ((lq ^ swz(lr)) << 4);
+    const int offB = (kCols + lr) * kPitch + ((lq ^ swz(lr)) << 4);
+    int slot = 0, k_left = KT;
+    int64_t wcol0 = first + wave * 16 * kVt;
+    for (int t = 0; t < steps; ++t) {
+        lm_stage_wait<kStages - 2, kW + kH>(steps - 1 - t);
+        if (t + kStages - 1 < steps) copy_next(slot == 0 ? kStages - 1 : slot - 1);
+        const unsigned char* const st = ring + slot * kStageBytes;
+#pragma unroll
+        for (int k = 0; k < kK / 32; ++k) {
+            bf16x8 a[kVt];
+#pragma unroll
+            for (int i = 0; i < kVt; ++i)
+                a[i] = *(const bf16x8*)(st + (offA ^ (k * 64)) + i * 16 * kPitch);
+#pragma unroll
+            for (int j = 0; j < kRt; ++j) {
+                const bf16x8 b = *(const bf16x8*)(st + (offB ^ (k * 64)) + j * 16 * kPitch);
+#pragma unroll
+                for (int i = 0; i < kVt; ++i)
+                    acc[k % kChains][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        a[i], b, acc[k % kChains][i][j], 0, 0, 0);
             }
-            packed = pack_kc(bk, bc);
-            unsigned long long o = __shfl_xor(packed, 16, 64);
-            packed = o > packed ? o : packed;
-            o = __shfl_xor(packed, 32, 64);
-            packed = o > packed ? o : packed;
-            update = have && packed_key(packed) >= best;
-        } else if (__ballot(have && sm >= best) != 0ull) {
-            int32_t c = 64;
-#pragma unroll
-            for (int e = 15; e >= 0; --e)                 // the lane's first equal column
-                c = (int32_t)u[e] == sm ? 16 * (e >> 2) + 4 * lq + (e & 3) : c;
-            c = min(c, __shfl_xor(c, 16, 64));
-            c = min(c, __shfl_xor(c, 32, 64));
-            packed = pack_kc(sm, wcol0 + c);
-            update = have && sm >= best;
         }
-        if (update && lq == 0) atomicMax(row_best + row0 + r, packed);
-        // The draft token's logit, where this lane holds its column.
-        const int64_t xo = (int64_t)s_draft[r] - wcol0;
-        const bool mine = have && xo >= 0 && xo < 64 && wcol0 + xo < N && (((int)xo >> 2) & 3) == lq;
-        if (__ballot(mine) != 0ull) {
-            const int e0 = ((int)xo >> 4) * 4 + ((int)xo & 3);
-            uint32_t z = u[0];
+        slot = slot == kStages - 1 ? 0 : slot + 1;
+        if (--k_left == 0) {                  // the tile is whole: rank it
 #pragma unroll
-            for (int e = 1; e < 16; ++e) z = e == e0 ? u[e] : z;
-            if (mine) row_draft_bits[row0 + r] = z;
+            for (int j = 0; j < kRt; ++j) {
+                uint32_t u[4 * kVt];
+#pragma unroll
+                for (int i = 0; i < kVt; ++i) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        float val = acc[0][i][j][v];
+                        if constexpr (kSpread) val += acc[kChains - 1][i][j][v];
+                        u[4 * i + v] = __float_as_uint(val);
+                    }
+                    acc[0][i][j] = acc[kChains - 1][i][j] = (f32x4)(0.0f);
+                }
+                const bool have = j * 16 + lr < M;
+                const unsigned long long p =
+                    lm_rank_rows<4 * kVt>(u, lq, wcol0, end, have, packed_key(top[j]));
+                top[j] = max(top[j], p);
+                lm_draft_logit<4 * kVt>(u, lq, wcol0, end, j * 16 + lr, have, s_draft[j * 16 + lr],
+                                        row_draft_bits);
+            }
+            k_left = KT;
+            wcol0 += kCols;
         }
     }
+
+    // The workgroup's greatest pair of each row updates the row's if it reaches
+    // it (read first: one atomic per row and workgroup at most).
+    __syncthreads();                          // the ring is read out
+    unsigned long long* const s_top = (unsigned long long*)ring;     // [kWaves][16 kRt]
+#pragma unroll
+    for (int j = 0; j < kRt; ++j)
+        if (lq == 0) s_top[wave * 16 * kRt + j * 16 + lr] = top[j];
+    __syncthreads();
+    if (tid < 16 * kRt && tid < M) {
+        unsigned long long p = 0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) p = max(p, s_top[w * 16 * kRt + tid]);
+        if (packed_key(p) >= lm_best_key(row_best, tid)) atomicMax(row_best + tid, p);
+    }
+}
+
+// As many workgroups as the CUs hold at once (160 KB of LDS each), none with
+// fewer than 64 columns where that can be helped.
+template <int kWaves, int kVt, int kRt, int kK, int kStages>
+void launch_lmhead_stream(hipStream_t stream, const void* hidden, const void* weight, int64_t rows,
+                          int64_t vocab, int64_t d, int num_cus, const int32_t* draft_tokens,
+                          unsigned long long* best, uint32_t* draft_bits) {
+    constexpr int kStageBytes = (16 * kVt * kWaves + 16 * kRt) * 2 * kK;
+    constexpr int kPerCu = 160 * 1024 / (kStageBytes * kStages + (16 * kRt + 63) / 64 * 256);
+    static_assert(kPerCu >= 1, "the ring fits the LDS of a CU");
+    const int64_t grid = min((vocab + 63) / 64, (int64_t)num_cus * kPerCu);
+    const bool spread = d % 2048 == 0;
+    auto kernel = spread ? asd_lmhead_stream_kernel<kWaves, kVt, kRt, kK, kStages, true>
+                         : asd_lmhead_stream_kernel<kWaves, kVt, kRt, kK, kStages, false>;
+    kernel<<<(unsigned)grid, 64 * kWaves, 0, stream>>>(
+        (const unsigned char*)hidden, (const unsigned char*)weight, (int32_t)rows, d,
+        (uint32_t)(vocab / grid), (uint32_t)(vocab % grid), draft_tokens, best, draft_bits);
 }
 
 template <int kNr>
@@ -1828,25 +2091,42 @@ hipError_t launch_commit(const int32_t* draft_tokens, const int32_t* block_lens,
 
 hipError_t launch_lmhead_verify(const void* hidden, const void* weight, int64_t d,
                                 int64_t vocab, int64_t rows, const CallArgs& a, void* workspace,
-                                hipStream_t stream) {
+                                int num_cus, hipStream_t stream) {
     unsigned char* ws = (unsigned char*)workspace;
     unsigned long long* best = (unsigned long long*)ws;
     uint32_t* draft_bits = (uint32_t*)(ws + lmhead_draft_offset(rows));
     asd_fill_u64_kernel<<<(unsigned)((rows + 255) / 256), 256, 0, stream>>>(best, rows, 0ull);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
-    const int64_t tiles_m = lmhead_row_tiles(rows);
-    // positions: row tiles x the weight tiles rounded up to whole groups
-    const int64_t tiles =
-        tiles_m * kLmGroup * (((vocab + kLmCols - 1) / kLmCols + kLmGroup - 1) / kLmGroup);
-    const int64_t grid = (tiles + 7) / 8 * 8;
-    static decltype(&launch_lmhead_tiles<1>) const launch[8] = {
-        launch_lmhead_tiles<1>, launch_lmhead_tiles<2>, launch_lmhead_tiles<3>,
-        launch_lmhead_tiles<4>, launch_lmhead_tiles<5>, launch_lmhead_tiles<6>,
-        launch_lmhead_tiles<7>, launch_lmhead_tiles<8>};
-    const int64_t nr = ((rows + tiles_m - 1) / tiles_m + 31) / 32;
-    launch[nr - 1](grid, stream, hidden, weight, rows, vocab, d, tiles_m, tiles, a.draft_tokens,
-                   best, draft_bits);
+    if (rows <= kLmStreamMaxRows) {
+        // The rows rounded up to a power of two of 16-row groups.  One group
+        // leaves LDS for two workgroups per CU (with four waves); for eight
+        // groups wide tiles read the hidden states less often (128 rows, d =
+        // 5,120: 334 us with 256 columns, 360 us with 128), but their ring is
+        // one stage shorter, which costs more where a CU has one narrow tile
+        // only (vocabulary 32,000, d = 1,024: 36.2 against 33.5 us).
+        auto launch = rows <= 16   ? launch_lmhead_stream<4, 1, 1, 128, 3>
+                      : rows <= 32 ? launch_lmhead_stream<8, 1, 2, 128, 3>
+                      : rows <= 64 ? launch_lmhead_stream<8, 1, 4, 128, 3>
+                      : vocab > (int64_t)128 * num_cus ? launch_lmhead_stream<8, 2, 8, 64, 3>
+                                                       : launch_lmhead_stream<8, 1, 8, 64, 4>;
+        launch(stream, hidden, weight, rows, vocab, d, num_cus, a.draft_tokens, best, draft_bits);
+    } else {
+        const int64_t tiles_m = lmhead_row_tiles(rows);
+        // positions: row tiles x the weight tiles rounded up to whole groups
+        const int64_t tiles =
+            tiles_m * kLmGroup * (((vocab + kLmCols - 1) / kLmCols + kLmGroup - 1) / kLmGroup);
+        const int64_t grid = (tiles + 7) / 8 * 8;
+        // A row tile's height: the rows spread evenly, in steps of 32.  More
+        // than 128 rows leave it above 128.
+        const int64_t nr = ((rows + tiles_m - 1) / tiles_m + 31) / 32;
+        auto launch = nr <= 5   ? launch_lmhead_tiles<5>
+                      : nr == 6 ? launch_lmhead_tiles<6>
+                      : nr == 7 ? launch_lmhead_tiles<7>
+                                : launch_lmhead_tiles<8>;
+        launch(grid, stream, hidden, weight, rows, vocab, d, tiles_m, tiles, a.draft_tokens, best,
+               draft_bits);
+    }
     if ((err = hipGetLastError()) != hipSuccess) return err;
     ScanArgs A = scan_args(a, rows, vocab, 2);
     A.splits = 1;

@@ -102,6 +102,27 @@ def test_row_tile_heights_bit_exact(rows):
     assert not bad, "differs in %s: %s" % (bad, describe(g, r))
 
 
+@pytest.mark.parametrize("rows,vocab,d", [(1, 40, 128), (16, 70001, 384), (17, 70001, 128),
+                                          (32, 33001, 384), (33, 70001, 128), (64, 33001, 384),
+                                          (65, 32768, 384), (100, 70001, 128), (128, 32769, 384),
+                                          (128, 150001, 128), (129, 33001, 128),
+                                          (9, 3001, 2048), (64, 17000, 2048), (120, 33001, 2048)])
+def test_weight_stream_shares_bit_exact(rows, vocab, d):
+    """Calls of up to 128 rows split the vocabulary evenly over the workgroups:
+    shares of several tiles with a part-full last one, K loops of one to six
+    steps in a ring of two to four stages, every row-group count."""
+    from asd_gpu import describe, mismatches
+    rng = np.random.default_rng(rows + vocab + d)
+    hidden, weight, draft = _exact_inputs(rng, rows, vocab, d)
+    lens = [2] * (rows // 3) + [rows % 3 - 1] * (rows % 3 > 0)
+    budget = np.stack([rng.uniform(0, 6, len(lens)), np.zeros(len(lens))], axis=1)
+    print("case lmhead stream rows %d vocab %d d %d" % (rows, vocab, d), flush=True)
+    g = _run(hidden, weight, draft, lens, 1.0, 2, budget)
+    r = oracle.lmhead_verify(hidden, weight, draft, lens, 1.0, 2, budget)
+    bad = mismatches(g, r)
+    assert not bad, "differs in %s: %s" % (bad, describe(g, r))
+
+
 @pytest.mark.parametrize("rows,vocab,d", [(130, 1027, 128), (40, 5000, 256), (300, 640, 128)])
 def test_nonfinite_and_negative_rows_bit_exact(rows, vocab, d):
     """Rows that the epilogue cannot rank by raw patterns: every logit negative,
