@@ -5,13 +5,21 @@ The functions here only marshal torch tensors (device memory) and the current
 HIP stream into the C calls; every step of the verifier runs in the library's
 HIP kernels.  There is no CPU fallback: if the library is missing or a call
 fails, an exception is raised.
+
+The per-round calls first try ``_asd_binding``, which does the same marshalling
+in native code for the ordinary arguments (tensors on the current device, dense,
+of the right types and shapes) and declines any others; the Python code below it
+then converts what it accepts and raises what it refuses.
 """
 import ctypes
+import functools
+import importlib
 import os
+import types
 
 import torch
 
-from .build import HASHED_SOURCES, LIBRARY, source_hash
+from .build import BINDING, BINDING_SOURCES, HASHED_SOURCES, LIBRARY, source_hash
 
 __all__ = ["asd_verify", "asd_verify_static", "asd_verify_ws", "asd_verify_ex", "asd_shard_argmax",
            "asd_verify_partials", "asd_opportunity", "asd_commit", "asd_verify_commit",
@@ -32,6 +40,7 @@ ASD_STATIC_SCRATCH_BYTES = 4 << 20
 _DTYPES = {torch.float32: ASD_F32, torch.bfloat16: ASD_BF16}
 
 _lib = None
+_fast = None
 
 
 class AsdError(RuntimeError):
@@ -116,6 +125,40 @@ def _load():
     lib.asd_release.restype = ctypes.c_int
     _lib = lib
     return lib
+
+
+def _load_fast():
+    """The native marshalling (``_asd_binding``), bound to the library's entry points."""
+    global _fast
+    lib = _load()
+    if not os.path.exists(BINDING):
+        raise RuntimeError("%s is not built; run __graft_entry__.build() first" % BINDING)
+    binding = importlib.import_module("._asd_binding", __name__)
+    built, current = binding.source_hash(), source_hash(BINDING_SOURCES)
+    if built != current:
+        raise RuntimeError("%s was built from other sources (built %s, sources %s); run "
+                           "__graft_entry__.build() again" % (BINDING, built, current))
+
+    def bind(function, entry):
+        return functools.partial(function, ctypes.cast(getattr(lib, entry), ctypes.c_void_p).value)
+
+    _fast = types.SimpleNamespace(
+        verify=bind(binding.verify, "asd_verify"),
+        verify_static=bind(binding.verify, "asd_verify_static"),
+        verify_ex=bind(binding.verify_ex, "asd_verify_ex"),
+        verify_commit=bind(binding.verify_commit, "asd_verify_commit"),
+        verify_partials=bind(binding.verify_partials, "asd_verify_partials"),
+        lmhead_verify=bind(binding.lmhead_verify, "asd_lmhead_verify"),
+        shard_argmax=bind(binding.shard_argmax, "asd_shard_argmax"),
+        opportunity=bind(binding.opportunity, "asd_opportunity"))
+    return _fast
+
+
+def _result(r, where):
+    """What a native call returned: its outputs, or the status it failed with."""
+    if type(r) is int:
+        raise AsdError(r, where)
+    return r
 
 
 def asd_status_string(status) -> str:
@@ -216,6 +259,11 @@ def asd_verify(logits, draft_tokens, block_lens, tau, exc_cap, budget, *, row_of
     Returns ``(accept_len, next_token)`` int32 tensors; the work is enqueued on
     the current stream of the logits' device.
     """
+    r = (_fast or _load_fast()).verify(logits, draft_tokens, block_lens, tau, exc_cap,
+                                       budget, row_offsets, out_accept_len, out_next_token,
+                                       out_argmax, out_regret)
+    if r is not None:
+        return _result(r, "asd_verify")
     _check_logits(logits)
     with torch.cuda.device(logits.device):
         args, acc, nxt, keep = _marshal(logits.device, logits.shape[0], draft_tokens, block_lens,
@@ -235,6 +283,11 @@ def asd_verify_static(logits, draft_tokens, block_lens, tau, exc_cap, budget, *,
     """``asd_verify`` with its workspace in the library's fixed per-device scratch
     (``asd_verify_static`` of ``include/asd.h``): the call allocates nothing.
     Calls that may overlap on one device race on that scratch."""
+    r = (_fast or _load_fast()).verify_static(logits, draft_tokens, block_lens, tau, exc_cap,
+                                              budget, row_offsets, out_accept_len, out_next_token,
+                                              out_argmax, out_regret)
+    if r is not None:
+        return _result(r, "asd_verify_static")
     _check_logits(logits)
     with torch.cuda.device(logits.device):
         args, acc, nxt, keep = _marshal(logits.device, logits.shape[0], draft_tokens, block_lens,
@@ -273,6 +326,12 @@ def asd_verify_ex(logits, draft_tokens, block_lens, tau, exc_cap, budget, *, fla
                   out_argmax=None, out_regret=None):
     """``asd_verify`` with flags (``ASD_GATE_RAW``) and an optional workspace
     (``asd_verify_ex`` of ``include/asd.h``)."""
+    if workspace is None:
+        r = (_fast or _load_fast()).verify_ex(logits, flags, draft_tokens, block_lens, tau, exc_cap,
+                                              budget, row_offsets, out_accept_len, out_next_token,
+                                              out_argmax, out_regret)
+        if r is not None:
+            return _result(r, "asd_verify_ex")
     if workspace is not None and (workspace.dtype != torch.uint8 or not workspace.is_contiguous()):
         raise ValueError("workspace must be a contiguous uint8 tensor")
     _check_logits(logits)
@@ -393,6 +452,12 @@ def asd_shard_argmax(shard_logits, vocab_offset, vocab, draft_tokens, out_partia
     draft_tokens  int32 [total_rows] (global ids)
     Returns the partials, an int32 tensor [total_rows, 4] (16 opaque bytes per row).
     """
+    if out_partials is not None:
+        r = (_fast or _load_fast()).shard_argmax(shard_logits, vocab_offset, vocab, draft_tokens,
+                                                 out_partials)
+        if r is not None:
+            _result(r, "asd_shard_argmax")
+            return out_partials
     if shard_logits.dim() != 2 or shard_logits.dtype not in _DTYPES or not shard_logits.is_cuda:
         raise ValueError("shard_logits must be a 2-D float32 or bfloat16 tensor on a GPU")
     if not shard_logits.is_contiguous():
@@ -430,6 +495,12 @@ def asd_verify_partials(partials, shard_vocab, vocab, draft_tokens, block_lens, 
               [k * shard_vocab, min((k + 1) * shard_vocab, vocab))
     Other arguments as for :func:`asd_verify`.  Returns ``(accept_len, next_token)``.
     """
+    r = (_fast or _load_fast()).verify_partials(partials, shard_vocab, vocab, draft_tokens,
+                                                block_lens, tau, exc_cap, budget, row_offsets,
+                                                out_accept_len, out_next_token, out_argmax,
+                                                out_regret)
+    if r is not None:
+        return _result(r, "asd_verify_partials")
     if partials.dtype != torch.int32 or partials.dim() != 3 or partials.shape[2] != 4 \
             or not partials.is_contiguous() or not partials.is_cuda:
         raise ValueError("partials must be a contiguous int32 (num_shards, total_rows, 4) GPU tensor")
@@ -455,6 +526,11 @@ def asd_opportunity(draft_tokens, row_argmax, row_regret, vocab, block_lens, tau
     taus   float32 [A]; ps int32 [P]
     counts int64 [A, P] and mismatches int64 [1]: uint64 accumulators, added to in place
     """
+    r = (_fast or _load_fast()).opportunity(draft_tokens, row_argmax, row_regret, vocab, block_lens,
+                                            taus, ps, counts, mismatches, row_offsets)
+    if r is not None:
+        _result(r, "asd_opportunity")
+        return
     dev = draft_tokens.device
     rows = draft_tokens.shape[0]
     for t, name, dt, shape in ((draft_tokens, "draft_tokens", torch.int32, (rows,)),
@@ -534,6 +610,13 @@ def asd_verify_commit(logits, draft_tokens, block_lens, tau, exc_cap, budget, to
              place as by :func:`asd_commit`.  workspace: None (library workspace) or a uint8
              tensor as for :func:`asd_verify_ws`.  Returns (accept_len, next_token).
     """
+    if workspace is None:
+        r = (_fast or _load_fast()).verify_commit(logits, tokens, seq_len, out_committed,
+                                                  draft_tokens, block_lens, tau, exc_cap, budget,
+                                                  row_offsets, out_accept_len, out_next_token,
+                                                  out_argmax, out_regret)
+        if r is not None:
+            return _result(r, "asd_verify_commit")
     _check_logits(logits)
     dev = logits.device
     n = block_lens.shape[0]
@@ -569,6 +652,11 @@ def asd_lmhead_verify(hidden, weight, draft_tokens, block_lens, tau, exc_cap, bu
 
     hidden  bf16 [total_rows, d]; weight bf16 [V, d]; other arguments as for :func:`asd_verify`.
     """
+    r = (_fast or _load_fast()).lmhead_verify(hidden, weight, draft_tokens, block_lens, tau, exc_cap,
+                                              budget, row_offsets, out_accept_len, out_next_token,
+                                              out_argmax, out_regret)
+    if r is not None:
+        return _result(r, "asd_lmhead_verify")
     for t, name in ((hidden, "hidden"), (weight, "weight")):
         if t.dim() != 2 or t.dtype != torch.bfloat16 or not t.is_cuda or not t.is_contiguous():
             raise ValueError("%s must be a contiguous 2-D bfloat16 GPU tensor" % name)

@@ -21,6 +21,9 @@ SOURCES = [os.path.join(CSRC, "asd_api.cpp"), os.path.join(CSRC, "asd_kernels.hi
 # Every file whose code goes into the library (sources and headers).
 HASHED_SOURCES = [os.path.join(CSRC, "asd_kernels.hip"), os.path.join(CSRC, "asd_plan.h"),
                   os.path.join(CSRC, "asd_api.cpp"), os.path.join(ROOT, "include", "asd.h")]
+# The binding's native marshalling (a CPython module over torch's C++ tensors).
+BINDING = os.path.join(HERE, "_asd_binding.so")
+BINDING_SOURCES = [os.path.join(CSRC, "asd_binding.cpp"), os.path.join(ROOT, "include", "asd.h")]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 HIP_FLAGS = [
@@ -54,5 +57,30 @@ def build_library(verbose: bool = False, output: str = LIBRARY, extra_flags=()) 
     return output
 
 
+def build_binding(verbose: bool = False, output: str = BINDING) -> str:
+    """The native marshalling, against the installed torch (host code only)."""
+    import sysconfig
+
+    import torch
+
+    base = os.path.dirname(torch.__file__)
+    include = [os.path.join(base, "include"),
+               os.path.join(base, "include", "torch", "csrc", "api", "include"),
+               "/opt/rocm/include", sysconfig.get_paths()["include"]]
+    cmd = ["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1",
+           "-DUSE_ROCM", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+           '-DASD_BINDING_HASH="%s"' % source_hash(BINDING_SOURCES)]
+    for path in include:
+        cmd += ["-isystem", path]
+    cmd += [BINDING_SOURCES[0], "-o", output + ".tmp", "-L" + os.path.join(base, "lib"), "-lc10",
+            "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    os.replace(output + ".tmp", output)
+    return output
+
+
 if __name__ == "__main__":
     print(build_library(verbose=True))
+    print(build_binding(verbose=True))
