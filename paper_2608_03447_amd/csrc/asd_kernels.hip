@@ -1282,7 +1282,6 @@ constexpr int kLmGroup = kLmheadGroup;   // weight tiles that share a hidden-sta
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef __amdgpu_buffer_rsrc_t rsrc_t;
 #define ASD_LDS __attribute__((address_space(3)))
 
 constexpr int kLmStreamMaxRows = 128;    // fewer rows stream the weights
@@ -1295,39 +1294,91 @@ constexpr int kRsrcWord3 = 0x00020000;   // raw buffer, 32-bit data format
 // one parity in such a group need distinct chunks: this gives them.
 __device__ __forceinline__ int lm_swz(int r) { return (r >> 1) & 7; }
 
-// One stage of one operand: tile rows 0 .. 32 kBlocks - 1, columns [k0b / 2,
-// k0b / 2 + 64).  Row r of the tile starts at byte r * K2 of the buffer.
+// Global -> LDS copies are written in asm: they fill LDS and no registers, and
+// the compiler, which cannot tell a ring's stages apart, would wait for all of
+// them before any fragment read.  The wait states before a copy cover a resource
+// or LDS address that has just been written.
+template <bool kNonTemporal>
+__device__ __forceinline__ void lm_lds_copy(u32x4 rsrc, int voff, int k0b, uint32_t lds) {
+    if constexpr (kNonTemporal)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
+                     :
+                     : "s"(lds), "v"(voff), "s"(rsrc), "s"(k0b)
+                     : "memory");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                     :
+                     : "s"(lds), "v"(voff), "s"(rsrc), "s"(k0b)
+                     : "memory");
+}
+
+__device__ __forceinline__ void lm_lds_copy_dword(u32x4 rsrc, int voff, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dword %1, %2, 0 offen lds"
+                 :
+                 : "s"(lds), "v"(voff), "s"(rsrc)
+                 : "memory");
+}
+
+template <int kOutstanding>
+__device__ __forceinline__ void lm_stage_barrier() {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(kOutstanding) : "memory");
+}
+
+// Waits for the oldest stage with `later` whole stages (at most kMost) of kPer
+// copies per wavefront behind it.
+template <int kMost, int kPer>
+__device__ __forceinline__ void lm_stage_wait(int later) {
+    if constexpr (kMost == 0) {
+        lm_stage_barrier<0>();
+    } else {
+        if (later >= kMost) lm_stage_barrier<kMost * kPer>();
+        else lm_stage_wait<kMost - 1, kPer>(later);
+    }
+}
+
+__device__ __forceinline__ u32x4 lm_rsrc(const unsigned char* base, int bytes) {
+    const uint64_t p = (uint64_t)base;
+    u32x4 r;
+    r.x = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)p);
+    r.y = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(p >> 32) & 0xffffu));
+    r.z = (uint32_t)__builtin_amdgcn_readfirstlane(bytes);
+    r.w = (uint32_t)kRsrcWord3;
+    return r;
+}
+
+// One stage of one operand: tile rows 0 .. 32 kBlocks - 1, bytes [k0b, k0b +
+// 128) of each.  Row r of the tile starts at byte r * K2 of the buffer.
 // Wavefronts 0..3, one per SIMD, copy; wavefront w copies the 1-KB blocks w,
 // w + 4, ..., each 8 rows, and lane l fills 16-B position l % 8 of row l / 8
 // with k-chunk (l % 8) ^ lm_swz(row).  The other wavefront of each SIMD issues
 // none, so it keeps the matrix core busy while its partner's copies are issued
 // (measured faster than all eight wavefronts copying).
 template <int kBlocks>
-__device__ __forceinline__ void lm_copy_stage(rsrc_t rs, int K2, int k0b, int wave, int lane,
-                                              __bf16* lds) {
+__device__ __forceinline__ void lm_copy_stage(u32x4 rs, int K2, int k0b, int wave, int lane,
+                                              uint32_t lds) {
     if (wave >= 4) return;
     const int c = (lane & 7) ^ lm_swz((wave & 1) * 8 + (lane >> 3));
     int voff = (wave * 8 + (lane >> 3)) * K2 + c * 16;
 #pragma unroll
     for (int u = 0; u < kBlocks; ++u) {
-        const int blk = u * 4 + wave;
         // The empty asm keeps the offsets in one register: hoisted out of the K
         // loop they would take one register per block, and spill.
         asm volatile("" : "+v"(voff));
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (void ASD_LDS*)(lds + blk * 512), 16, voff,
-                                                 k0b, 0, 0);
+        lm_lds_copy<false>(rs, voff, k0b, lds + (u * 4 + wave) * 1024);
         voff += 32 * K2;
     }
 }
 
 struct LmCtx {
-    rsrc_t rh, rw;
+    u32x4 rh, rw;
+    const unsigned char* ring;
+    uint32_t lds;        // LDS address of the ring
     int K2, wave, lane;
-    int offA, offB;      // this lane's first fragment of slice 0 (elements)
+    int offA, offB;      // bytes from a stage to this lane's first fragment of slice 0
 };
 
-__device__ __forceinline__ bf16x8 lm_frag(const __bf16* stage, int off, int slice, int tile) {
-    return *(const bf16x8*)(stage + (off ^ (slice * 32)) + tile * 16 * kLmK);
+__device__ __forceinline__ bf16x8 lm_frag(const LmCtx& x, int off, int tile) {
+    return *(const bf16x8*)(x.ring + off + tile * 16 * 2 * kLmK);
 }
 
 // c += a b.  Written in asm so that an accumulator keeps its registers: the
@@ -1351,7 +1402,7 @@ __device__ __forceinline__ void lm_mfma_drain(f32x4 (&acc)[4][kNr]) {
 }
 
 // MFMAs of row groups [kFrom, kTo) of one slice.  With `kRead`, the fragments
-// of slice `kSliceNext` of stage (Wn, Hn) replace the consumed ones: the weight
+// at bytes `fa` and `fb` of the ring replace the consumed ones: the weight
 // fragments go to `an`, and each row group's hidden-state fragment into the
 // register it was consumed from, right after its MFMAs.  The reads whose
 // registers are free from the start (the weights' and those of the row groups
@@ -1362,9 +1413,9 @@ __device__ __forceinline__ void lm_mfma_drain(f32x4 (&acc)[4][kNr]) {
 // hold the compiler to this order: an earlier read of a fragment would need a
 // second register for it, and registers are what this kernel is short of; a
 // later one would be waited for.
-template <int kNr, int kFrom, int kTo, bool kRead, int kSliceNext>
-__device__ __forceinline__ void lm_slice(const LmCtx& x, const __bf16* Wn, const __bf16* Hn,
-                                         const bf16x8 (&a)[4], bf16x8 (&an)[4], bf16x8 (&b)[kNr],
+template <int kNr, int kFrom, int kTo, bool kRead>
+__device__ __forceinline__ void lm_slice(const LmCtx& x, int fa, int fb, const bf16x8 (&a)[4],
+                                         bf16x8 (&an)[4], bf16x8 (&b)[kNr],
                                          f32x4 (&acc)[4][kNr]) {
     constexpr int kFree = 4 + kFrom, kGroups = kTo - kFrom;
     constexpr int kEven = kGroups > 0 ? (kFree + kGroups - 1) / kGroups : 0;
@@ -1382,35 +1433,35 @@ __device__ __forceinline__ void lm_slice(const LmCtx& x, const __bf16* Wn, const
                 for (int e = (i * n + 2) / 4; e < ((i + 1) * n + 2) / 4; ++e) {
                     const int f = first + e;
                     __builtin_amdgcn_sched_barrier(0);
-                    if (f < 4) an[f < 4 ? f : 0] = lm_frag(Wn, x.offA, kSliceNext, f);
-                    else b[f < 4 ? 0 : f - 4] = lm_frag(Hn, x.offB, kSliceNext, f - 4);
+                    if (f < 4) an[f < 4 ? f : 0] = lm_frag(x, fa, f);
+                    else b[f < 4 ? 0 : f - 4] = lm_frag(x, fb, f - 4);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
         }
         if constexpr (kRead) {
             __builtin_amdgcn_sched_barrier(0);
-            b[j] = lm_frag(Hn, x.offB, kSliceNext, j);
+            b[j] = lm_frag(x, fb, j);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
 }
 
-// One K step on stage (Wc, Hc), whose slice 0 fragments are in (a0, b).  The
-// stage after next (k0b) is copied into (Wc, Hc) once it is no longer read.
+// One K step on the weight stage at ring byte wc and the hidden-state stage at
+// hc, whose slice 0 fragments are in (a0, b); (wn, hn) are the next step's.  Once
+// they are no longer read, hc takes the copies of the stage after next (byte kh
+// of each row) and wc those of the one after that (kw).
 template <int kNr, int kJ0>
-__device__ __forceinline__ void lm_step(const LmCtx& x, __bf16* Wc, __bf16* Hc, const __bf16* Wn,
-                                        const __bf16* Hn, int k0b, bf16x8 (&a0)[4],
-                                        bf16x8 (&a1)[4], bf16x8 (&b)[kNr],
-                                        f32x4 (&acc)[4][kNr]) {
-    lm_slice<kNr, 0, kNr, true, 1>(x, Wc, Hc, a0, a1, b, acc);
+__device__ __forceinline__ void lm_step(const LmCtx& x, int wc, int wn, int hc, int hn, int kh,
+                                        int kw, bf16x8 (&a0)[4], bf16x8 (&a1)[4],
+                                        bf16x8 (&b)[kNr], f32x4 (&acc)[4][kNr]) {
+    lm_slice<kNr, 0, kNr, true>(x, (x.offA ^ kLmK) + wc, (x.offB ^ kLmK) + hc, a0, a1, b, acc);
     __builtin_amdgcn_sched_barrier(0);
-    lm_slice<kNr, 0, kJ0, false, 0>(x, Wn, Hn, a1, a0, b, acc);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this lane's copies of (Wn, Hn)
-    __syncthreads();
-    lm_copy_stage<8>(x.rw, x.K2, k0b, x.wave, x.lane, Wc);
-    lm_copy_stage<kNr>(x.rh, x.K2, k0b, x.wave, x.lane, Hc);
-    lm_slice<kNr, kJ0, kNr, true, 0>(x, Wn, Hn, a1, a0, b, acc);
+    lm_slice<kNr, 0, kJ0, false>(x, 0, 0, a1, a0, b, acc);
+    lm_stage_barrier<8>();        // all but this wavefront's copies of the weights after next
+    lm_copy_stage<kNr>(x.rh, x.K2, kh, x.wave, x.lane, x.lds + hc);
+    lm_copy_stage<8>(x.rw, x.K2, kw, x.wave, x.lane, x.lds + wc);
+    lm_slice<kNr, kJ0, kNr, true>(x, x.offA + wn, x.offB + hn, a1, a0, b, acc);
     __builtin_amdgcn_sched_barrier(0);
 }
 
@@ -1507,12 +1558,11 @@ __global__ __launch_bounds__(kLmThreads) void asd_lmhead_kernel(
     uint32_t* __restrict__ row_draft_bits) {
     constexpr int kRows = 32 * kNr;
     constexpr int kJ0 = kNr >= 6 ? 2 : 1;
-    __shared__ __attribute__((aligned(1024))) __bf16 W0[kLmCols * kLmK];
-    __shared__ __attribute__((aligned(1024))) __bf16 H0[kRows * kLmK];
-    __shared__ __attribute__((aligned(1024))) __bf16 W1[kLmCols * kLmK];
-    __shared__ __attribute__((aligned(1024))) __bf16 H1[kRows * kLmK];
-    __shared__ int32_t s_draft[kRows];
-    __shared__ int32_t s_best[kRows];
+    constexpr int kW = kLmCols * 2 * kLmK, kH = kRows * 2 * kLmK;     // bytes of a stage
+    constexpr int kH0 = 3 * kW, kH1 = kH0 + kH;
+    __shared__ __attribute__((aligned(1024))) unsigned char ring[3 * kW + 2 * kH];
+    int32_t* const s_draft = (int32_t*)ring;             // once the K loop is over
+    int32_t* const s_best = s_draft + kRows;
 
     // XCD-aware order: workgroup i runs on XCD i % 8, and each XCD takes a run
     // of consecutive positions.  Positions run over groups of kLmGroup weight
@@ -1535,51 +1585,61 @@ __global__ __launch_bounds__(kLmThreads) void asd_lmhead_kernel(
 
     LmCtx x;
     x.K2 = (int)(K * 2);
-    x.rh = __builtin_amdgcn_make_buffer_rsrc((void*)(hidden + row0 * x.K2), (short)0,
-                                             (int)(min((int64_t)kRows, M - row0) * x.K2),
-                                             kRsrcWord3);
-    x.rw = __builtin_amdgcn_make_buffer_rsrc((void*)(weight + col0 * x.K2), (short)0,
-                                             (int)(min((int64_t)kLmCols, N - col0) * x.K2),
-                                             kRsrcWord3);
+    x.rh = lm_rsrc(hidden + row0 * x.K2, (int)(min((int64_t)kRows, M - row0) * x.K2));
+    x.rw = lm_rsrc(weight + col0 * x.K2, (int)(min((int64_t)kLmCols, N - col0) * x.K2));
+    x.ring = ring;
+    x.lds = (uint32_t)(uintptr_t)(unsigned char ASD_LDS*)ring;
     x.wave = wave;
     x.lane = lane;
     const int chunk = (lane >> 4) ^ lm_swz(lane & 15);
-    x.offA = (wv * 64 + (lane & 15)) * kLmK + chunk * 8;
-    x.offB = (wr * 16 * kNr + (lane & 15)) * kLmK + chunk * 8;
+    x.offA = (wv * 64 + (lane & 15)) * 2 * kLmK + chunk * 16;
+    x.offB = (wr * 16 * kNr + (lane & 15)) * 2 * kLmK + chunk * 16;
 
     // K / 64 is even.  Copies past the last stage are clamped to it: they
     // refill a stage that is no longer read, and the fragments read after the
     // last stage are never used.
     const int KT = (int)(K / kLmK);
-    lm_copy_stage<8>(x.rw, x.K2, 0, wave, lane, W0);
-    lm_copy_stage<kNr>(x.rh, x.K2, 0, wave, lane, H0);
-    if (tid < kRows) {                        // each row's draft token and greatest key so far
-        const bool have = row0 + tid < M;
-        s_draft[tid] = have ? draft_tokens[row0 + tid] : -1;
-        s_best[tid] = have ? lm_best_key(row_best, row0 + tid) : 0x7fffffff;
+    int32_t my_draft = -1, my_best = 0x7fffffff;   // of row tid, for the epilogue
+    if (tid < kRows && row0 + tid < M) {
+        my_draft = draft_tokens[row0 + tid];
+        my_best = lm_best_key(row_best, row0 + tid);
     }
+    asm volatile("" : "+v"(my_draft), "+v"(my_best));   // here, not after the copies
+    lm_copy_stage<kNr>(x.rh, x.K2, 0, wave, lane, x.lds + kH0);
+    lm_copy_stage<8>(x.rw, x.K2, 0, wave, lane, x.lds);
+    lm_copy_stage<8>(x.rw, x.K2, 2 * kLmK, wave, lane, x.lds + kW);
     f32x4 acc[4][kNr];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int j = 0; j < kNr; ++j) acc[i][j] = (f32x4)(0.0f);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    lm_copy_stage<8>(x.rw, x.K2, 2 * kLmK, wave, lane, W1);
-    lm_copy_stage<kNr>(x.rh, x.K2, 2 * kLmK, wave, lane, H1);
+    lm_stage_barrier<8>();
+    lm_copy_stage<kNr>(x.rh, x.K2, 2 * kLmK, wave, lane, x.lds + kH1);
+    lm_copy_stage<8>(x.rw, x.K2, min(2, KT - 1) * 2 * kLmK, wave, lane, x.lds + 2 * kW);
     bf16x8 a0[4], a1[4], b[kNr];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) a0[i] = lm_frag(W0, x.offA, 0, i);
+    for (int i = 0; i < 4; ++i) a0[i] = lm_frag(x, x.offA, i);
 #pragma unroll
-    for (int j = 0; j < kNr; ++j) b[j] = lm_frag(H0, x.offB, 0, j);
+    for (int j = 0; j < kNr; ++j) b[j] = lm_frag(x, x.offB + kH0, j);
     lm_mfma_drain<kNr>(acc);                  // the zeros are written before an MFMA reads them
     __builtin_amdgcn_s_waitcnt(kWaitLds);     // else the loop's first wait counts scalar loads too
+    int w0 = 0, w1 = kW, w2 = 2 * kW;         // weight stages of steps s, s + 1 and s + 2
     for (int s = 0; s < KT; s += 2) {
-        lm_step<kNr, kJ0>(x, W0, H0, W1, H1, min(s + 2, KT - 1) * 2 * kLmK, a0, a1, b, acc);
-        lm_step<kNr, kJ0>(x, W1, H1, W0, H0, min(s + 3, KT - 1) * 2 * kLmK, a0, a1, b, acc);
+        auto at = [&](int step) { return min(step, KT - 1) * 2 * kLmK; };
+        lm_step<kNr, kJ0>(x, w0, w1, kH0, kH1, at(s + 2), at(s + 3), a0, a1, b, acc);
+        lm_step<kNr, kJ0>(x, w1, w2, kH1, kH0, at(s + 3), at(s + 4), a0, a1, b, acc);
+        const int t = w0;
+        w0 = w2;
+        w2 = w1;
+        w1 = t;
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no copy outlives the main loop
     lm_mfma_drain<kNr>(acc);
+    lm_stage_barrier<0>();                    // no copy and no fragment read outlives the K loop
+    if (tid < kRows) {
+        s_draft[tid] = my_draft;
+        s_best[tid] = my_best;
+    }
+    __syncthreads();
 
     // ---- epilogue
     const int64_t wcol0 = col0 + wv * 64;
@@ -1635,61 +1695,9 @@ __global__ __launch_bounds__(kLmThreads) void asd_lmhead_kernel(
 // that took these rows before: 9 rows 236 us (6.6 TB/s) against 425; 32 rows
 // 249 / 424; 64 rows 274 / 415; 128 rows 334 / 433.
 //
-// The copies are written in asm: they fill LDS and no registers, and the
-// compiler, which cannot tell a ring's stages apart, would wait for all of them
-// before any fragment read.  Each K step waits until at most the copies of the
-// later stages are outstanding (they complete in order), then meets the other
-// wavefronts: the step's stage is whole, and the stage before it is read out
-// and takes the next copies.  The wait states before a copy cover a resource
-// or LDS address that has just been written.
-template <bool kNonTemporal>
-__device__ __forceinline__ void lm_lds_copy(u32x4 rsrc, int voff, int k0b, uint32_t lds) {
-    if constexpr (kNonTemporal)
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
-                     :
-                     : "s"(lds), "v"(voff), "s"(rsrc), "s"(k0b)
-                     : "memory");
-    else
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                     :
-                     : "s"(lds), "v"(voff), "s"(rsrc), "s"(k0b)
-                     : "memory");
-}
-
-__device__ __forceinline__ void lm_lds_copy_dword(u32x4 rsrc, int voff, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dword %1, %2, 0 offen lds"
-                 :
-                 : "s"(lds), "v"(voff), "s"(rsrc)
-                 : "memory");
-}
-
-template <int kOutstanding>
-__device__ __forceinline__ void lm_stage_barrier() {
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(kOutstanding) : "memory");
-}
-
-// Waits for the oldest stage with `later` whole stages (at most kMost) of kPer
-// copies per wavefront behind it.
-template <int kMost, int kPer>
-__device__ __forceinline__ void lm_stage_wait(int later) {
-    if constexpr (kMost == 0) {
-        lm_stage_barrier<0>();
-    } else {
-        if (later >= kMost) lm_stage_barrier<kMost * kPer>();
-        else lm_stage_wait<kMost - 1, kPer>(later);
-    }
-}
-
-__device__ __forceinline__ u32x4 lm_rsrc(const unsigned char* base, int bytes) {
-    const uint64_t p = (uint64_t)base;
-    u32x4 r;
-    r.x = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)p);
-    r.y = (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(p >> 32) & 0xffffu));
-    r.z = (uint32_t)__builtin_amdgcn_readfirstlane(bytes);
-    r.w = (uint32_t)kRsrcWord3;
-    return r;
-}
-
+// Each K step waits until at most the copies of the later stages are outstanding
+// (they complete in order), then meets the other wavefronts: the step's stage is
+// whole, and the stage before it is read out and takes the next copies.
 template <int kWaves, int kVt, int kRt, int kK, int kStages, bool kSpread>
 __global__ __launch_bounds__(64 * kWaves) void asd_lmhead_stream_kernel(
     const unsigned char* __restrict__ hidden, const unsigned char* __restrict__ weight,
