@@ -111,7 +111,7 @@ typedef struct {
  *    a_i = 0, next token = -1, ledger untouched.
  *  Both cases also set a bit of the device error word (asd_device_error).
  *
- * Small calls (at most 512 row tiles and 8 requests, the latency-bound
+ * Small calls (at most 96 row tiles and 8 requests, the latency-bound
  * regime of single-request decoding) that are not being captured run as one
  * kernel launch instead of two: the last row tile to finish runs the scan.
  * This form needs a zeroed counter, so it runs only with a library workspace

@@ -627,6 +627,56 @@ __device__ __forceinline__ void tile_best(const unsigned char* row_ptr, const Ro
     }
 }
 
+// ------------------------------------- outputs read within the same launch
+//
+// In the single-launch form the last tile reads what the others wrote, from
+// other XCDs.  These write and read past the XCD's own caches (agent-scope
+// relaxed atomics: sc1), 64 bits at a time, so that neither side writes back or
+// invalidates an L2; with kShared unset they are plain accesses.
+template <bool kShared>
+__device__ __forceinline__ void put(TilePartial* to, const TilePartial& t) {
+    if constexpr (kShared) {
+        unsigned long long* const w = (unsigned long long*)to;
+        __hip_atomic_store(w, t.packed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(w + 1, ((unsigned long long)t.draft_bits << 32) | t.bits,
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else {
+        *to = t;
+    }
+}
+template <bool kShared>
+__device__ __forceinline__ void put(RowRecord* to, const RowRecord& r) {
+    if constexpr (kShared)
+        __hip_atomic_store((unsigned long long*)to, __builtin_bit_cast(unsigned long long, r),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else
+        *to = r;
+}
+template <bool kShared>
+__device__ __forceinline__ TilePartial get(const TilePartial* from) {
+    if constexpr (kShared) {
+        unsigned long long* const w = (unsigned long long*)from;
+        TilePartial t;
+        t.packed = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned long long v =
+            __hip_atomic_load(w + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        t.bits = (uint32_t)v;
+        t.draft_bits = (uint32_t)(v >> 32);
+        return t;
+    } else {
+        return *from;
+    }
+}
+template <bool kShared>
+__device__ __forceinline__ RowRecord get(const RowRecord* from) {
+    if constexpr (kShared)
+        return __builtin_bit_cast(
+            RowRecord, __hip_atomic_load((unsigned long long*)from, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT));
+    else
+        return *from;
+}
+
 // ----------------------------------------------------------- stage 1 kernel
 
 // One tile of the row pass, the body of the row kernels.  `logits` rows hold
@@ -636,7 +686,7 @@ __device__ __forceinline__ void tile_best(const unsigned char* row_ptr, const Ro
 // rows, or one shard of each row); otherwise the row is one tile and writes its
 // record.  `pre` runs once, right after the tile's first loads are issued (for
 // the caller's own loads).  Thread 0 writes; every thread returns.
-template <int EB, typename Pre>
+template <int EB, bool kShared, typename Pre>
 __device__ __forceinline__ void row_tile(
     const unsigned char* __restrict__ logits, int64_t vocab, int64_t col_offset, int splits,
     int64_t chunk_vecs, const int32_t* __restrict__ draft_tokens,
@@ -694,7 +744,7 @@ __device__ __forceinline__ void row_tile(
         tp.packed = packed;
         tp.bits = bits;
         tp.draft_bits = draft_bits;      // meaningful in the owning tile only
-        partials[blockIdx.x] = tp;
+        put<kShared>(partials + blockIdx.x, tp);
         return;
     }
 
@@ -708,7 +758,7 @@ __device__ __forceinline__ void row_tile(
         rec.regret = __builtin_huge_valf();
         rec.y_flags = (uint32_t)y | kMismatchBit | kBadDraftBit;
     }
-    records[row] = rec;
+    put<kShared>(records + row, rec);
     if (out_argmax) out_argmax[row] = y;
 }
 
@@ -726,11 +776,11 @@ __global__ __launch_bounds__(kRowThreads) __attribute__((amdgpu_waves_per_eu(5))
     TilePartial* __restrict__ partials, RowRecord* __restrict__ records,
     int32_t* __restrict__ out_argmax, int32_t num_requests,
     const int32_t* __restrict__ block_lens, int64_t* __restrict__ packed_offsets) {
-    row_tile<EB>(logits, vocab, col_offset, splits, chunk_vecs, draft_tokens, partials, records,
-                 out_argmax, [&] {
-                     if (blockIdx.x == 0 && packed_offsets != nullptr)
-                         write_packed_offsets(num_requests, block_lens, packed_offsets);
-                 });
+    row_tile<EB, false>(logits, vocab, col_offset, splits, chunk_vecs, draft_tokens, partials,
+                        records, out_argmax, [&] {
+                            if (blockIdx.x == 0 && packed_offsets != nullptr)
+                                write_packed_offsets(num_requests, block_lens, packed_offsets);
+                        });
 }
 
 // ----------------------------------------------------------- stage 2 kernel
@@ -767,6 +817,7 @@ struct ScanArgs {
 };
 
 // Greatest (key, column) of a row's split partials and the gathered draft logit.
+template <bool kShared>
 __device__ __forceinline__ void combine_row(const ScanArgs& A, int64_t row, int32_t x,
                                             unsigned long long& packed, uint32_t& bits,
                                             uint32_t& draft_bits) {
@@ -800,7 +851,7 @@ __device__ __forceinline__ void combine_row(const ScanArgs& A, int64_t row, int3
         TilePartial tp[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j)
-            if (s0 + j < A.splits) tp[j] = parts[(s0 + j) * stride];
+            if (s0 + j < A.splits) tp[j] = get<kShared>(parts + (s0 + j) * stride);
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             if (s0 + j < A.splits) {
@@ -840,6 +891,7 @@ __device__ __forceinline__ RequestIn load_request(const ScanArgs& A, int64_t i) 
     return q;
 }
 
+template <bool kShared>
 __device__ __forceinline__ void scan_request(const ScanArgs& A, int64_t i, int64_t o,
                                              const RequestIn& q) {
     const int lane = threadIdx.x & 63;
@@ -875,7 +927,7 @@ __device__ __forceinline__ void scan_request(const ScanArgs& A, int64_t i, int64
         if (have) {
             const int64_t row = o + p;
             if (A.records != nullptr) {
-                const RowRecord rec = A.records[row];
+                const RowRecord rec = get<kShared>(A.records + row);
                 y = rec.y_flags & kArgmaxMask;
                 mism = (rec.y_flags & kMismatchBit) != 0u;
                 bad = (rec.y_flags & kBadDraftBit) != 0u;
@@ -884,7 +936,7 @@ __device__ __forceinline__ void scan_request(const ScanArgs& A, int64_t i, int64
                 const int32_t x = A.draft_tokens[row];
                 unsigned long long packed;
                 uint32_t bits, draft_bits;
-                combine_row(A, row, x, packed, bits, draft_bits);
+                combine_row<kShared>(A, row, x, packed, bits, draft_bits);
                 y = (uint32_t)packed_col(packed);
                 bad = !(x >= 0 && (int64_t)x < A.vocab);
                 mism = bad || (uint32_t)x != y;
@@ -959,7 +1011,7 @@ __global__ __launch_bounds__(kScanThreads) void asd_scan_kernel(const ScanArgs A
         if (row < A.total_rows) {
             unsigned long long packed;
             uint32_t bits, draft_bits;
-            combine_row(A, row, -1, packed, bits, draft_bits);
+            combine_row<false>(A, row, -1, packed, bits, draft_bits);
             A.out_argmax[row] = packed_col(packed);
         }
         return;
@@ -984,22 +1036,24 @@ __global__ __launch_bounds__(kScanThreads) void asd_scan_kernel(const ScanArgs A
         for (int off = 32; off >= 1; off >>= 1) part += __shfl_xor(part, off, 64);
         o = part;
     }
-    scan_request(A, i, o, q);
+    scan_request<false>(A, i, o, q);
 }
 
 // ---------------------------------------------- single-launch verification
 //
 // For plans with few tiles and few requests the call is bound by latency, and
 // the second launch of the scan is a large share of it.  Here the row pass and
-// the scan run in one launch: every tile counts itself done on a counter, with
-// release order after its record or partial, and the one tile that finds
-// itself last (acquire order) runs Algorithm 1 for every request, one
-// wavefront per request, writes the argmax of split rows and resets the
-// counter to zero for the next call.  No tile waits for another.  The counter
-// must be zero when the call starts: it lives in a header of the library's
-// workspaces that is zeroed when they are allocated, and every call leaves it
-// at zero.
-// Small plans have at most two tiles per CU, so the kernel takes the registers
+// the scan run in one launch: every tile counts itself done on a counter once
+// its record or partial is written, and the one tile that finds itself last
+// runs Algorithm 1 for every request, one wavefront per request, writes the
+// argmax of split rows and resets the counter to zero for the next call.  No
+// tile waits for another.  The records and partials pass by the L2s (put and
+// get above), so the counter needs no release and no acquire, each of which
+// costs a pass over an L2: 9 rows of 32,000 f32 take 7.7 us on the GPU, 8.2
+// with them, and 270 tiles 11.3 for 14.3.  The counter must be zero when the
+// call starts: it lives in a header of the library's workspaces that is zeroed
+// when they are allocated, and every call leaves it at zero.
+// Small plans have less than a tile per CU, so the kernel takes the registers
 // it needs (no occupancy bound).
 static_assert(kSingleLaunchMaxRequests <= 2 * kWaves, "two requests per wavefront at most");
 
@@ -1034,26 +1088,28 @@ __global__ __launch_bounds__(kRowThreads) void asd_row_scan_kernel(const unsigne
             }
         }
     };
-    row_tile<EB>(logits, vocab, 0, splits, chunk_vecs, A.draft_tokens, partials, records,
-                 splits == 1 ? A.out_argmax : nullptr, preload);
+    row_tile<EB, true>(logits, vocab, 0, splits, chunk_vecs, A.draft_tokens, partials, records,
+                       splits == 1 ? A.out_argmax : nullptr, preload);
     __shared__ int s_last;
     if (threadIdx.x == 0) {
+        // This thread's output has reached the memory that every XCD reads.
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         const unsigned prev =
-            __hip_atomic_fetch_add(counter, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         s_last = prev == gridDim.x - 1;
+        asm volatile("" ::: "memory");    // no tile's output is read ahead of this
     }
     __syncthreads();
     if (!s_last) return;
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");   // every tile's output, for every thread
 
 #pragma unroll
     for (int j = 0; j < 2; ++j)
-        if (wave + 4 * j < A.num_requests) scan_request(A, wave + 4 * j, o[j], q[j]);
+        if (wave + 4 * j < A.num_requests) scan_request<true>(A, wave + 4 * j, o[j], q[j]);
     if (splits > 1 && A.out_argmax) {
         for (int64_t row = threadIdx.x; row < A.total_rows; row += kRowThreads) {
             unsigned long long packed;
             uint32_t bits, draft_bits;
-            combine_row(A, row, -1, packed, bits, draft_bits);
+            combine_row<true>(A, row, -1, packed, bits, draft_bits);
             A.out_argmax[row] = packed_col(packed);
         }
     }

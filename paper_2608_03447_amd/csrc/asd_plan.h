@@ -96,8 +96,14 @@ Plan make_plan(int elem_bytes, int64_t vocab, int64_t rows, int32_t num_requests
 
 // Plans small enough for one launch (row pass and scan in one kernel; see
 // asd_row_scan_kernel): few tiles, and few requests, since the last tile scans
-// every request with its four wavefronts.
-constexpr int64_t kSingleLaunchMaxTiles = 512;
+// every request with its four wavefronts.  A second launch costs the host about
+// 2.4 us of 8.7; counting on one counter costs each tile of the single launch a
+// wait for its output and about 10 ns of the counter.  Time on the GPU, back to
+// back, one launch against two: 63 tiles 7.7 and 7.2 us, 75 tiles 8.8 and 8.5,
+// 270 tiles 11.3 and 9.1, 396 tiles 14.0 and 9.5, 720 tiles 20.1 and 10.4 (15 us
+// with the counter split over several lines of memory).  So up to 96 tiles the
+// saved launch is worth more, and two launches are faster above.
+constexpr int64_t kSingleLaunchMaxTiles = 96;
 constexpr int32_t kSingleLaunchMaxRequests = 8;   // two per wavefront of the last tile
 inline bool single_launch(const Plan& p) {
     return p.rows * p.splits <= kSingleLaunchMaxTiles &&

@@ -154,3 +154,37 @@ def test_single_launch_on_two_streams_in_flight():
         assert np.array_equal(accs[k].cpu().numpy(), np.stack(r_acc)), k
         assert np.array_equal(nxts[k].cpu().numpy(), np.stack(r_nxt)), k
         assert np.array_equal(budgets[k].cpu().numpy().view(np.uint32), ledger.view(np.uint32)), k
+
+
+@pytest.mark.parametrize("k", [12, 13])          # 7 tiles a row: 91 and 98 tiles
+def test_both_sides_of_the_tile_limit_match_the_oracle(k):
+    """The largest single launch of this vocabulary and the smallest call above
+    it, 300 calls each with new logits in the same buffer: no call reads what an
+    earlier one left in the workspace."""
+    vocab, calls = 32000, 300
+    rng = np.random.default_rng(k)
+    host = rng.standard_normal((8, k + 1, vocab)).astype(np.float32)
+    draft = host.argmax(axis=2).astype(np.int32)
+    draft[:, k // 2] = (draft[:, k // 2] + 1) % vocab
+    lens, tau, cap = np.array([k], np.int32), np.array([1.0], np.float32), np.array([2], np.int32)
+    budget = np.array([[3.0, 0.0]], np.float32)
+    refs = [oracle.verify(host[i], draft[i], lens, tau, cap, budget) for i in range(8)]
+    sets = [torch.from_numpy(x).to(DEV) for x in host]
+    drafts = [torch.from_numpy(x).to(DEV) for x in draft]
+    g = [torch.from_numpy(x).to(DEV) for x in (lens, tau, cap, budget)]
+    logits = torch.empty_like(sets[0])
+    outs = []
+    for c in range(calls):
+        logits.copy_(sets[c % 8])
+        ledger = g[3].clone()
+        amax = torch.empty(k + 1, dtype=torch.int32, device=DEV)
+        acc, nxt = asd.asd_verify(logits, drafts[c % 8], g[0], g[1], g[2], ledger, out_argmax=amax)
+        outs.append((acc, nxt, ledger, amax))
+    torch.cuda.synchronize()
+    for c, (acc, nxt, ledger, amax) in enumerate(outs):
+        ref = refs[c % 8]
+        assert np.array_equal(acc.cpu().numpy(), ref["accept_len"]), c
+        assert np.array_equal(nxt.cpu().numpy(), ref["next_token"]), c
+        assert np.array_equal(ledger.cpu().numpy().view(np.uint32),
+                              ref["budget"].view(np.uint32)), c
+        assert np.array_equal(amax.cpu().numpy(), ref["argmax"]), c
