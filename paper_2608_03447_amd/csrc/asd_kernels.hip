@@ -371,17 +371,19 @@ __device__ void write_packed_offsets(int32_t num_requests, const int32_t* __rest
     }
 }
 
-// Row offsets of one workgroup's requests [first, first + count), count <=
-// kScanThreads, into s_off: row_offsets[i] when given, else the packed layout
+// Row offsets of one workgroup's requests [first, first + count), count <= its
+// 64 kBlockWaves threads, into s_off: row_offsets[i] when given, else the packed layout
 // o_i = sum_{j<i} (max(K_j, 0) + 1).  For the packed layout the whole workgroup
 // sums the row counts of the requests before `first`, then scans its own, so
 // no request count is too large and nothing is written to global memory.
 // Ends with a barrier.
-__device__ void block_offsets(int32_t num_requests, const int32_t* __restrict__ block_lens,
-                              const int64_t* __restrict__ row_offsets, int64_t first, int count,
-                              int64_t* s_off) {
-    __shared__ long long s_before[kWaves];
-    __shared__ long long s_mine[kWaves];
+template <int kBlockWaves>
+__device__ __forceinline__ void block_offsets(int32_t num_requests,
+                                              const int32_t* __restrict__ block_lens,
+                                              const int64_t* __restrict__ row_offsets,
+                                              int64_t first, int count, int64_t* s_off) {
+    __shared__ long long s_before[kBlockWaves];
+    __shared__ long long s_mine[kBlockWaves];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (row_offsets) {
         if (tid < count) s_off[tid] = row_offsets[first + tid];
@@ -389,7 +391,7 @@ __device__ void block_offsets(int32_t num_requests, const int32_t* __restrict__ 
         return;
     }
     long long before = 0;
-    for (int64_t j = tid; j < first; j += blockDim.x) {
+    for (int64_t j = tid; j < first; j += 64 * kBlockWaves) {
         const int32_t K = block_lens[j];
         before += (long long)(K > 0 ? K : 0) + 1;
     }
@@ -406,7 +408,8 @@ __device__ void block_offsets(int32_t num_requests, const int32_t* __restrict__ 
     if (lane == 0) s_before[wave] = before;
     __syncthreads();
     long long base = 0, earlier = 0;
-    for (int w = 0; w < (int)(blockDim.x >> 6); ++w) {
+#pragma unroll
+    for (int w = 0; w < kBlockWaves; ++w) {
         base += s_before[w];
         earlier += (w < wave) ? s_mine[w] : 0;
     }
@@ -1172,9 +1175,19 @@ hipError_t launch_row(int elem_bytes, dim3 grid, hipStream_t stream, Args... arg
 // ones of the mask above the position, carried across 64-position chunks from
 // the block's end).  A mismatch at position i with r_i <= tau and a following
 // run of at least p greedy drafts (which also gives i + p <= K) counts for
-// (tau, p); each (tau, p) count of a chunk is one ballot's popcount.  Counts
-// gather in LDS, then in the caller's uint64 accumulators.
-__global__ __launch_bounds__(kScanThreads) void asd_opportunity_kernel(
+// (tau, p): with lanes = pairs, the wavefront walks the chunk's mismatches and
+// every lane tests its pair against each.  Counts gather in LDS, then in the
+// caller's uint64 accumulators.
+//
+// A chain of memory round trips bounds it, so the pairs' thresholds are read
+// with the block lengths.  Workgroups have 16 wavefronts because all of them add
+// to the same few accumulators, one after another.  256 requests of 16 drafts,
+// 35 pairs: 4.4 us a call; with four wavefronts, one ballot per pair and the
+// thresholds read in the loop 7.8 us.
+constexpr int kOppWaves = 16;
+constexpr int kOppMostRequests = 64;     // of one workgroup
+
+__global__ __launch_bounds__(64 * kOppWaves) void asd_opportunity_kernel(
     const int32_t* __restrict__ draft_tokens, const int32_t* __restrict__ row_argmax,
     const float* __restrict__ row_regret, int64_t vocab, int32_t num_requests,
     int64_t total_rows, const int32_t* __restrict__ block_lens,
@@ -1182,24 +1195,31 @@ __global__ __launch_bounds__(kScanThreads) void asd_opportunity_kernel(
     const int32_t* __restrict__ ps, int32_t num_ps, unsigned long long* __restrict__ counts,
     unsigned long long* __restrict__ mismatches, int per_block) {
     __shared__ uint32_t s_counts[kMaxOpportunityPairs];
+    __shared__ float s_tau[kMaxOpportunityPairs];      // of pair k
+    __shared__ int32_t s_p[kMaxOpportunityPairs];
     __shared__ uint32_t s_mism;
-    __shared__ int64_t s_off[kScanThreads];
+    __shared__ int64_t s_off[kOppMostRequests];
+    __shared__ int32_t s_len[kOppMostRequests];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int pairs = num_taus * num_ps;
-    for (int k = tid; k < pairs; k += kScanThreads) s_counts[k] = 0u;
-    if (tid == 0) s_mism = 0u;
     const int64_t first = (int64_t)blockIdx.x * per_block;
     const int count = (int)min((int64_t)per_block, (int64_t)num_requests - first);
-    block_offsets(num_requests, block_lens, row_offsets, first, count, s_off);   // + barrier
+    if (tid < count) s_len[tid] = block_lens[first + tid];
+    for (int k = tid; k < pairs; k += 64 * kOppWaves) {
+        s_tau[k] = taus[k / num_ps];
+        s_p[k] = ps[k % num_ps];
+        s_counts[k] = 0u;
+    }
+    if (tid == 0) s_mism = 0u;
+    block_offsets<kOppWaves>(num_requests, block_lens, row_offsets, first, count, s_off);   // + barrier
 
-    for (int kq = wave; kq < count; kq += kScanThreads / 64) {    // wave-uniform
-        const int64_t i = first + kq;
-        const int32_t K = block_lens[i];
+    for (int kq = wave; kq < count; kq += kOppWaves) {            // wave-uniform
+        const int32_t K = __builtin_amdgcn_readfirstlane(s_len[kq]);
         const int64_t o = s_off[kq];
         if (K >= 0 && o >= 0 && o + (int64_t)K < total_rows) {
             // Chunks from the block's end: `carry` = greedy run starting at the
             // first position after the chunk.
-            int64_t carry = 0;
+            int32_t carry = 0;
             uint32_t mism_total = 0;
             const int64_t nchunks = ((int64_t)K + 63) / 64;
             for (int64_t c = nchunks - 1; c >= 0; --c) {
@@ -1209,42 +1229,44 @@ __global__ __launch_bounds__(kScanThreads) void asd_opportunity_kernel(
                 float r = 0.0f;
                 if (have) {
                     const int32_t x = draft_tokens[o + p];
-                    match = x >= 0 && (int64_t)x < vocab && x == row_argmax[o + p];
+                    const int32_t y = row_argmax[o + p];
                     r = row_regret[o + p];
+                    match = x >= 0 && (int64_t)x < vocab && x == y;
                 }
                 const unsigned long long m = __ballot(have && match);
                 const int n_here = (int)min((int64_t)64, (int64_t)K - c * 64);
                 // trailing ones of the mask above this lane, within the chunk
                 const unsigned long long above = lane < 63 ? (m >> (lane + 1)) : 0ull;
                 const int ones = (int)__builtin_ctzll(~above);   // < 64 - lane
-                const int64_t run = (lane + 1 + ones >= n_here) ? (int64_t)(n_here - 1 - lane) + carry
-                                                                : (int64_t)ones;
-                const bool mism = have && !match;
-                const unsigned long long mm = __ballot(mism);
+                const int32_t run = lane + 1 + ones >= n_here ? n_here - 1 - lane + carry : ones;
+                const unsigned long long mm = __ballot(have && !match);
                 mism_total += (uint32_t)__builtin_popcountll(mm);
                 if (mm) {
-                    for (int a = 0; a < num_taus; ++a) {
-                        const float t = taus[a];
-                        const unsigned long long ma = __ballot(mism && r <= t);
-                        if (!ma) continue;
-                        for (int b = 0; b < num_ps; ++b) {
-                            const int64_t need = ps[b];
-                            const unsigned long long mab = __ballot(mism && r <= t && run >= need);
-                            if (lane == 0 && mab)
-                                atomicAdd(&s_counts[a * num_ps + b],
-                                          (uint32_t)__builtin_popcountll(mab));
+                    for (int k0 = 0; k0 < pairs; k0 += 64) {
+                        const int k = k0 + lane;
+                        const bool pair = k < pairs;
+                        const float t = pair ? s_tau[k] : 0.0f;
+                        const int32_t need = pair ? s_p[k] : 0;
+                        uint32_t n = 0;
+                        for (unsigned long long w = mm; w != 0ull; w &= w - 1ull) {
+                            const int j = __builtin_ctzll(w);
+                            const float rj = __builtin_bit_cast(
+                                float, lane_u32(__builtin_bit_cast(uint32_t, r), j));
+                            const int32_t run_j = (int32_t)lane_u32((uint32_t)run, j);
+                            n += rj <= t && run_j >= need;
                         }
+                        if (pair && n != 0) atomicAdd(&s_counts[k], n);
                     }
                 }
                 // greedy run starting at this chunk's first position
                 const int lead = m == ~0ull ? 64 : (int)__builtin_ctzll(~m);
-                carry = lead >= n_here ? (int64_t)n_here + carry : (int64_t)lead;
+                carry = lead >= n_here ? n_here + carry : lead;
             }
             if (lane == 0 && mism_total) atomicAdd(&s_mism, mism_total);
         }
     }
     __syncthreads();
-    for (int k = tid; k < pairs; k += kScanThreads)
+    for (int k = tid; k < pairs; k += 64 * kOppWaves)
         if (s_counts[k]) atomicAdd(counts + k, (unsigned long long)s_counts[k]);
     if (tid == 0 && s_mism) atomicAdd(mismatches, (unsigned long long)s_mism);
 }
@@ -1266,7 +1288,7 @@ __global__ __launch_bounds__(kScanThreads) void asd_commit_kernel(
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t first = (int64_t)blockIdx.x * per_block;
     const int count = (int)min((int64_t)per_block, (int64_t)num_requests - first);
-    block_offsets(num_requests, block_lens, row_offsets, first, count, s_off);
+    block_offsets<kScanThreads / 64>(num_requests, block_lens, row_offsets, first, count, s_off);
     for (int k = wave; k < count; k += kScanThreads / 64) {       // wave-uniform
         const int64_t i = first + k;
         const int32_t K_given = block_lens[i];
@@ -2122,8 +2144,8 @@ hipError_t launch_verify_partials(const void* partials, int num_shards, int64_t 
 // wavefront while the packed layout's per-workgroup prefix sums stay short
 // (at most 8,192 requests before a workgroup), else 64, so that those sums
 // total about n^2 / 128 loads.
-static int requests_per_block(int32_t num_requests, const int64_t* row_offsets) {
-    return (row_offsets || num_requests <= 8192) ? kScanThreads / 64 : 64;
+static int requests_per_block(int32_t num_requests, const int64_t* row_offsets, int waves) {
+    return (row_offsets || num_requests <= 8192) ? waves : kOppMostRequests;
 }
 
 hipError_t launch_opportunity(const int32_t* draft_tokens, const int32_t* row_argmax,
@@ -2132,9 +2154,9 @@ hipError_t launch_opportunity(const int32_t* draft_tokens, const int32_t* row_ar
                               const int64_t* row_offsets, const float* taus, int32_t num_taus,
                               const int32_t* ps, int32_t num_ps, unsigned long long* counts,
                               unsigned long long* mismatches, hipStream_t stream) {
-    const int per_block = requests_per_block(num_requests, row_offsets);
+    const int per_block = requests_per_block(num_requests, row_offsets, kOppWaves);
     const unsigned blocks = (unsigned)((num_requests + per_block - 1) / per_block);
-    asd_opportunity_kernel<<<blocks, kScanThreads, 0, stream>>>(
+    asd_opportunity_kernel<<<blocks, 64 * kOppWaves, 0, stream>>>(
         draft_tokens, row_argmax, row_regret, vocab, num_requests, total_rows, block_lens,
         row_offsets, taus, num_taus, ps, num_ps, counts, mismatches, per_block);
     return hipGetLastError();
@@ -2145,7 +2167,7 @@ hipError_t launch_commit(const int32_t* draft_tokens, const int32_t* block_lens,
                          const int32_t* accept_len, const int32_t* next_token, int32_t* tokens,
                          int64_t capacity, int64_t* seq_len, int32_t* committed,
                          hipStream_t stream) {
-    const int per_block = requests_per_block(num_requests, row_offsets);
+    const int per_block = requests_per_block(num_requests, row_offsets, kScanThreads / 64);
     const unsigned blocks = (unsigned)((num_requests + per_block - 1) / per_block);
     asd_commit_kernel<<<blocks, kScanThreads, 0, stream>>>(
         draft_tokens, block_lens, row_offsets, num_requests, total_rows, accept_len, next_token,

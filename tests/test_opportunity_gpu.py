@@ -94,3 +94,22 @@ def test_opportunity_explicit_offsets_and_invalid_requests():
     counts, m = gpu_counts(draft, y, regret, vocab, lens, TAUS, PS, row_offsets=offs)
     ref_c, ref_m = oracle.opportunity(draft, y, regret, vocab, lens, TAUS, PS, row_offsets=offs)
     assert m == ref_m and np.array_equal(counts, ref_c)
+
+
+@pytest.mark.parametrize("num_taus,num_ps", [(1, 1), (8, 8), (13, 5), (32, 32), (1, 1024)])
+@pytest.mark.parametrize("num_requests", [15, 16, 17, 33])
+def test_opportunity_pair_and_request_counts_around_a_workgroup(num_taus, num_ps, num_requests):
+    """1, 64, 65 and 1,024 pairs (a lane each, 64 at a time) over request counts
+    around the 16 of a workgroup."""
+    rng = np.random.default_rng(num_requests * 2000 + num_taus * num_ps)
+    vocab = 40
+    lens = rng.integers(0, 70, num_requests).astype(np.int32)
+    rows = int(np.sum(lens + 1))
+    y = rng.integers(0, vocab, rows).astype(np.int32)
+    draft = np.where(rng.random(rows) < 0.6, y, rng.integers(-1, vocab + 1, rows)).astype(np.int32)
+    regret = rng.choice(np.array([0.0, 0.25, 1.0, 3.0, np.inf, np.nan], np.float32), rows)
+    taus = rng.choice(np.array([-1.0, 0.0, 0.25, 2.0, np.inf, np.nan], np.float32), num_taus)
+    ps = rng.integers(-2, 70, num_ps).astype(np.int32)
+    counts, m = gpu_counts(draft, y, regret, vocab, lens, taus, ps)
+    ref_c, ref_m = oracle.opportunity(draft, y, regret, vocab, lens, taus, ps)
+    assert m == ref_m and np.array_equal(counts, ref_c)
