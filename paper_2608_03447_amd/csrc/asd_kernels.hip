@@ -1330,13 +1330,17 @@ __global__ __launch_bounds__(kScanThreads) void asd_commit_kernel(
 // element e): row l % 16 of the operand's 16, k = 8 (l / 16) + e; accumulator v
 // of lane l is column 4 (l / 16) + v, hidden-state row l % 16.
 //
-// K steps of 64 go through two LDS stages per operand, rows of 128 B.  Global
-// -> LDS copies are buffer loads that write LDS directly (no VGPR staging);
-// rows past M or N read as zero from the buffer resource.  The 16-B chunk c of
-// row r is stored at chunk c ^ lm_swz(r), which keeps both the copies and the
-// fragment reads free of bank conflicts.  The two stages are distinct arrays so
-// the compiler can tell that a copy into one stage does not alias the fragment
-// reads from the other.
+// K steps of 64 go through LDS stages of 128-B rows, three for the weights and
+// two for the hidden states.  Global -> LDS copies are buffer loads that write
+// LDS directly (no VGPR staging); rows past M or N read as zero from the buffer
+// resource.  The 16-B chunk c of row r is stored at chunk c ^ lm_swz(r), which
+// keeps both the copies and the fragment reads free of bank conflicts.  The
+// weights miss L2 far more often than the hidden states, which every workgroup
+// reads, so their copies get two K steps to land: with two stages each, making
+// every weight copy an L2 hit took 544 rows (d = 5,120) from 781 to 575 us, every
+// hidden-state copy to 783.  Three stages, same box: 544 rows 802 -> 690 us; 4,352
+// rows 4,753 -> 4,530; 2,816 rows of 129,280 columns, d = 7,168, 3,659 -> 3,472.
+// (Touching the weights ahead, one load per line, was slower: 904 us and up.)
 //
 // Software pipeline of one wavefront: the fragments of the next k-slice of 32
 // are read while the current slice's MFMAs issue.  The barrier that publishes
@@ -1344,19 +1348,26 @@ __global__ __launch_bounds__(kScanThreads) void asd_commit_kernel(
 // the last reads of the current stage; the next stage's first reads and the
 // copies into the freed stage overlap the rest.
 //
-// What bounds it is the chip's power.  4,352 rows, 151,936 columns, d = 5,120,
-// Gaussian data: 4.68-4.73 ms (1,430-1,446 TFLOP/s) at 1.6 GHz with the matrix
-// cores 85% busy; on data of ones the same kernel clocks 2.4 GHz.  So it is
+// What bounds large calls is the chip's power.  4,352 rows, 151,936 columns, d =
+// 5,120, Gaussian data: 4.53-4.56 ms (1,485-1,495 TFLOP/s) at 1.7 GHz with the
+// matrix cores 83% busy; on data of ones the kernel clocks 2.4 GHz.  So it is
 // built to spend little energy per flop: 16x16x32 MFMAs, which move half the
 // accumulator bytes of 32x32x16 (registers-only probe 1,955 against 1,725
 // TFLOP/s; this kernel's 32x32x16 predecessor took 5.08 ms on the same box),
 // operands repeated from one MFMA to the next, and an epilogue within lanes
 // (0.085 ms of the call; the predecessor's went through LDS, 0.15-0.2 ms).
-// With every copy an L2 hit it would take 4.32 ms, with no copies 3.77 ms.
+// With every copy an L2 hit it would take 4.2 ms, with no copies 3.7 ms.
 constexpr int kLmCols = 256;             // weight rows of a tile
 constexpr int kLmK = 64;
 constexpr int kLmThreads = 512;
-constexpr int kLmGroup = kLmheadGroup;   // weight tiles that share a hidden-state row tile
+// Up to this many row tiles read a weight tile, at about the same time: its
+// copies are non-temporal, as in the stream kernel below.  255 rows, d = 5,120:
+// 444 us cached, 386 us so; 144 rows of 128,256 columns, d = 7,168: 346 and 319;
+// two row tiles, 408 rows of 129,280 columns, d = 7,168: 676 and 630; 272 rows,
+// d = 5,120: 470 and 457.  With three, which miss each other's copies more often,
+// it loses: 544 rows 692 and 716.
+constexpr int kLmOnceMaxRowTiles = 2;
+static_assert(kLmOnceMaxRowTiles <= kLmheadFewRowTiles, "these take the smaller groups");
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -1431,7 +1442,7 @@ __device__ __forceinline__ u32x4 lm_rsrc(const unsigned char* base, int bytes) {
 // with k-chunk (l % 8) ^ lm_swz(row).  The other wavefront of each SIMD issues
 // none, so it keeps the matrix core busy while its partner's copies are issued
 // (measured faster than all eight wavefronts copying).
-template <int kBlocks>
+template <int kBlocks, bool kOnce>
 __device__ __forceinline__ void lm_copy_stage(u32x4 rs, int K2, int k0b, int wave, int lane,
                                               uint32_t lds) {
     if (wave >= 4) return;
@@ -1442,7 +1453,7 @@ __device__ __forceinline__ void lm_copy_stage(u32x4 rs, int K2, int k0b, int wav
         // The empty asm keeps the offsets in one register: hoisted out of the K
         // loop they would take one register per block, and spill.
         asm volatile("" : "+v"(voff));
-        lm_lds_copy<false>(rs, voff, k0b, lds + (u * 4 + wave) * 1024);
+        lm_lds_copy<kOnce>(rs, voff, k0b, lds + (u * 4 + wave) * 1024);
         voff += 32 * K2;
     }
 }
@@ -1529,16 +1540,16 @@ __device__ __forceinline__ void lm_slice(const LmCtx& x, int fa, int fb, const b
 // hc, whose slice 0 fragments are in (a0, b); (wn, hn) are the next step's.  Once
 // they are no longer read, hc takes the copies of the stage after next (byte kh
 // of each row) and wc those of the one after that (kw).
-template <int kNr, int kJ0>
+template <int kNr, int kJ0, bool kOnce>
 __device__ __forceinline__ void lm_step(const LmCtx& x, int wc, int wn, int hc, int hn, int kh,
                                         int kw, bf16x8 (&a0)[4], bf16x8 (&a1)[4],
                                         bf16x8 (&b)[kNr], f32x4 (&acc)[4][kNr]) {
-    lm_slice<kNr, 0, kNr, true>(x, (x.offA ^ kLmK) + wc, (x.offB ^ kLmK) + hc, a0, a1, b, acc);
+    lm_slice<kNr, 0, kNr, true>(x, (x.offA ^ 64) + wc, (x.offB ^ 64) + hc, a0, a1, b, acc);
     __builtin_amdgcn_sched_barrier(0);
     lm_slice<kNr, 0, kJ0, false>(x, 0, 0, a1, a0, b, acc);
     lm_stage_barrier<8>();        // all but this wavefront's copies of the weights after next
-    lm_copy_stage<kNr>(x.rh, x.K2, kh, x.wave, x.lane, x.lds + hc);
-    lm_copy_stage<8>(x.rw, x.K2, kw, x.wave, x.lane, x.lds + wc);
+    lm_copy_stage<kNr, false>(x.rh, x.K2, kh, x.wave, x.lane, x.lds + hc);
+    lm_copy_stage<8, kOnce>(x.rw, x.K2, kw, x.wave, x.lane, x.lds + wc);
     lm_slice<kNr, kJ0, kNr, true>(x, x.offA + wn, x.offB + hn, a1, a0, b, acc);
     __builtin_amdgcn_sched_barrier(0);
 }
@@ -1628,7 +1639,7 @@ __device__ __forceinline__ int32_t lm_best_key(const unsigned long long* row_bes
         __hip_atomic_load(row_best + row, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
 
-template <int kNr>
+template <int kNr, int kGroup, bool kOnce>
 __global__ __launch_bounds__(kLmThreads) void asd_lmhead_kernel(
     const unsigned char* __restrict__ hidden, const unsigned char* __restrict__ weight,
     int64_t M, int64_t N, int64_t K, uint32_t tiles_m, uint32_t tiles,
@@ -1643,17 +1654,17 @@ __global__ __launch_bounds__(kLmThreads) void asd_lmhead_kernel(
     int32_t* const s_best = s_draft + kRows;
 
     // XCD-aware order: workgroup i runs on XCD i % 8, and each XCD takes a run
-    // of consecutive positions.  Positions run over groups of kLmGroup weight
+    // of consecutive positions.  Positions run over groups of kGroup weight
     // tiles (slowest), row tiles, then the weight tiles of the group (fastest):
     // the tiles of a group start together and read each hidden-state slice
     // once between them from L2, and a group of weight tiles serves the row
     // tiles that the XCD runs alongside it.
     const uint32_t linear = blockIdx.x % 8 * (gridDim.x / 8) + blockIdx.x / 8;
-    const uint32_t group = linear / (kLmGroup * tiles_m), within = linear % (kLmGroup * tiles_m);
+    const uint32_t group = linear / (kGroup * tiles_m), within = linear % (kGroup * tiles_m);
     // Divisions run on the vector unit: back to scalars, or each copy loops
     // over the values its resource could have.
-    const int rt = __builtin_amdgcn_readfirstlane((int)(within / kLmGroup));
-    const int ct = __builtin_amdgcn_readfirstlane((int)(group * kLmGroup + within % kLmGroup));
+    const int rt = __builtin_amdgcn_readfirstlane((int)(within / kGroup));
+    const int ct = __builtin_amdgcn_readfirstlane((int)(group * kGroup + within % kGroup));
     if (linear >= tiles || (int64_t)ct * kLmCols >= N) return;
     const int64_t row0 = (int64_t)rt * kRows, col0 = (int64_t)ct * kLmCols;
 
@@ -1683,17 +1694,17 @@ __global__ __launch_bounds__(kLmThreads) void asd_lmhead_kernel(
         my_best = lm_best_key(row_best, row0 + tid);
     }
     asm volatile("" : "+v"(my_draft), "+v"(my_best));   // here, not after the copies
-    lm_copy_stage<kNr>(x.rh, x.K2, 0, wave, lane, x.lds + kH0);
-    lm_copy_stage<8>(x.rw, x.K2, 0, wave, lane, x.lds);
-    lm_copy_stage<8>(x.rw, x.K2, 2 * kLmK, wave, lane, x.lds + kW);
+    lm_copy_stage<kNr, false>(x.rh, x.K2, 0, wave, lane, x.lds + kH0);
+    lm_copy_stage<8, kOnce>(x.rw, x.K2, 0, wave, lane, x.lds);
+    lm_copy_stage<8, kOnce>(x.rw, x.K2, 2 * kLmK, wave, lane, x.lds + kW);
     f32x4 acc[4][kNr];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int j = 0; j < kNr; ++j) acc[i][j] = (f32x4)(0.0f);
     lm_stage_barrier<8>();
-    lm_copy_stage<kNr>(x.rh, x.K2, 2 * kLmK, wave, lane, x.lds + kH1);
-    lm_copy_stage<8>(x.rw, x.K2, min(2, KT - 1) * 2 * kLmK, wave, lane, x.lds + 2 * kW);
+    lm_copy_stage<kNr, false>(x.rh, x.K2, 2 * kLmK, wave, lane, x.lds + kH1);
+    lm_copy_stage<8, kOnce>(x.rw, x.K2, min(2, KT - 1) * 2 * kLmK, wave, lane, x.lds + 2 * kW);
     bf16x8 a0[4], a1[4], b[kNr];
 #pragma unroll
     for (int i = 0; i < 4; ++i) a0[i] = lm_frag(x, x.offA, i);
@@ -1704,8 +1715,8 @@ __global__ __launch_bounds__(kLmThreads) void asd_lmhead_kernel(
     int w0 = 0, w1 = kW, w2 = 2 * kW;         // weight stages of steps s, s + 1 and s + 2
     for (int s = 0; s < KT; s += 2) {
         auto at = [&](int step) { return min(step, KT - 1) * 2 * kLmK; };
-        lm_step<kNr, kJ0>(x, w0, w1, kH0, kH1, at(s + 2), at(s + 3), a0, a1, b, acc);
-        lm_step<kNr, kJ0>(x, w1, w2, kH1, kH0, at(s + 3), at(s + 4), a0, a1, b, acc);
+        lm_step<kNr, kJ0, kOnce>(x, w0, w1, kH0, kH1, at(s + 2), at(s + 3), a0, a1, b, acc);
+        lm_step<kNr, kJ0, kOnce>(x, w1, w2, kH1, kH0, at(s + 3), at(s + 4), a0, a1, b, acc);
         const int t = w0;
         w0 = w2;
         w2 = w1;
@@ -1938,9 +1949,12 @@ void launch_lmhead_stream(hipStream_t stream, const void* hidden, const void* we
 template <int kNr>
 void launch_lmhead_tiles(int64_t grid, hipStream_t stream, const void* hidden, const void* weight,
                          int64_t rows, int64_t vocab, int64_t d, int64_t tiles_m, int64_t tiles,
-                         const int32_t* draft_tokens, unsigned long long* best,
+                         int64_t group, const int32_t* draft_tokens, unsigned long long* best,
                          uint32_t* draft_bits) {
-    asd_lmhead_kernel<kNr><<<(unsigned)grid, kLmThreads, 0, stream>>>(
+    auto kernel = tiles_m <= kLmOnceMaxRowTiles ? asd_lmhead_kernel<kNr, kLmheadGroupFew, true>
+                  : group == kLmheadGroupFew    ? asd_lmhead_kernel<kNr, kLmheadGroupFew, false>
+                                                : asd_lmhead_kernel<kNr, kLmheadGroup, false>;
+    kernel<<<(unsigned)grid, kLmThreads, 0, stream>>>(
         (const unsigned char*)hidden, (const unsigned char*)weight, rows, vocab, d, (uint32_t)tiles_m,
         (uint32_t)tiles, draft_tokens, best, draft_bits);
 }
@@ -2199,9 +2213,10 @@ hipError_t launch_lmhead_verify(const void* hidden, const void* weight, int64_t 
         launch(stream, hidden, weight, rows, vocab, d, num_cus, a.draft_tokens, best, draft_bits);
     } else {
         const int64_t tiles_m = lmhead_row_tiles(rows);
+        const int64_t group = tiles_m <= kLmheadFewRowTiles ? kLmheadGroupFew : kLmheadGroup;
         // positions: row tiles x the weight tiles rounded up to whole groups
         const int64_t tiles =
-            tiles_m * kLmGroup * (((vocab + kLmCols - 1) / kLmCols + kLmGroup - 1) / kLmGroup);
+            tiles_m * group * (((vocab + kLmCols - 1) / kLmCols + group - 1) / group);
         const int64_t grid = (tiles + 7) / 8 * 8;
         // A row tile's height: the rows spread evenly, in steps of 32.  More
         // than 128 rows leave it above 128.
@@ -2210,7 +2225,8 @@ hipError_t launch_lmhead_verify(const void* hidden, const void* weight, int64_t 
                       : nr == 6 ? launch_lmhead_tiles<6>
                       : nr == 7 ? launch_lmhead_tiles<7>
                                 : launch_lmhead_tiles<8>;
-        launch(grid, stream, hidden, weight, rows, vocab, d, tiles_m, tiles, a.draft_tokens, best,
+        launch(grid, stream, hidden, weight, rows, vocab, d, tiles_m, tiles, group,
+               a.draft_tokens, best,
                draft_bits);
     }
     if ((err = hipGetLastError()) != hipSuccess) return err;

@@ -172,6 +172,11 @@ inline size_t lmhead_workspace_bytes(int64_t rows, int32_t num_requests) {
 // LM-head tiles are 256 columns by at most 256 rows; grid positions run over
 // whole groups of kLmheadGroup weight tiles (the kernel's tile order).
 constexpr int kLmheadGroup = 4;
+// With few row tiles, groups of two: the workgroups that share a weight tile
+// then start closer together (544 rows, d = 5,120, 702 -> 692 us; 1,020 rows 1,161 ->
+// 1,148; 1,275 rows of 32,000 columns, d = 4,096, 263 -> 262), while 17 row tiles
+// want four (4,352 rows 4,772 us, in twos 4,881).
+constexpr int kLmheadGroupFew = 2, kLmheadFewRowTiles = 5;
 inline int64_t lmhead_row_tiles(int64_t rows) { return (rows + 255) / 256; }
 hipError_t launch_lmhead_verify(const void* hidden, const void* weight, int64_t d,
                                 int64_t vocab, int64_t rows, const CallArgs& a, void* workspace,

@@ -102,6 +102,25 @@ def test_row_tile_heights_bit_exact(rows):
     assert not bad, "differs in %s: %s" % (bad, describe(g, r))
 
 
+@pytest.mark.parametrize("rows,d", [(129, 128), (255, 256), (256, 384), (257, 128), (512, 640),
+                                    (513, 256), (1280, 384), (1281, 512)])
+def test_row_tile_counts_and_short_k_loops_bit_exact(rows, d):
+    """The weights' copies and the tile order follow the number of row tiles (1,
+    2, to 5, above), and the three weight stages turn over every three K steps of
+    64: edges of the row tiles, with 2 to 10 steps, exact regime, and weight tiles
+    that leave the last group of two and of four short."""
+    from asd_gpu import describe, mismatches
+    rng = np.random.default_rng(rows + d)
+    hidden, weight, draft = _exact_inputs(rng, rows, 1100, d)
+    lens = [15] * (rows // 16) + [rows % 16 - 1] * (rows % 16 > 0)
+    budget = np.stack([rng.uniform(0, 6, len(lens)), np.zeros(len(lens))], axis=1)
+    print("case lmhead row tiles, rows %d d %d" % (rows, d), flush=True)
+    g = _run(hidden, weight, draft, lens, 1.0, 2, budget)
+    r = oracle.lmhead_verify(hidden, weight, draft, lens, 1.0, 2, budget)
+    bad = mismatches(g, r)
+    assert not bad, "differs in %s: %s" % (bad, describe(g, r))
+
+
 @pytest.mark.parametrize("rows,vocab,d", [(1, 40, 128), (16, 70001, 384), (17, 70001, 128),
                                           (32, 33001, 384), (33, 70001, 128), (64, 33001, 384),
                                           (65, 32768, 384), (100, 70001, 128), (128, 32769, 384),
