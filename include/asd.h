@@ -403,8 +403,11 @@ asd_status asd_verify_commit(const void *logits, asd_dtype dtype, int64_t vocab,
  * weight          bf16 [vocab, d], row-major: the output (LM-head) weights.
  * d               hidden size, a multiple of 128, 128 <= d <= 2^20.  Both base
  *                 addresses 16-byte aligned.
- * Logits are binary32 sums of the bf16 products (accumulated on the matrix
- * cores in an order of their own); a greatest logit of zero is taken as +0.
+ * Logits are binary32 sums of the bf16 products, accumulated on the matrix
+ * cores in an order of their own: the same for every column and every row
+ * count, so equal weight rows tie exactly (the lower index wins) and a row's
+ * outputs do not depend on the rows beside it.  A greatest logit of zero is
+ * taken as +0.
  * The other arguments and all outputs are those of asd_verify.  Uses the
  * library workspace of (device, stream) like asd_verify (allocated on first
  * use, never during stream capture).

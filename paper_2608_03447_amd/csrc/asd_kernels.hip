@@ -1773,12 +1773,14 @@ __global__ __launch_bounds__(kLmThreads) void asd_lmhead_kernel(
 //  - Each copied row is at least a whole 128-B line per step.  With fragments
 //    loaded straight into registers (64 B of 16 rows per load) the same call
 //    took 293 us.
-//  - With kSpread, workgroups start their K loops at different steps: rows that
-//    are a multiple of 4 KB apart otherwise fall on few memory channels at a
-//    time (151,936 columns, 32 rows, d = 2,048: 124.5 us in step, 106.6 us so;
-//    d = 4,096: 202.6 and 197.9; d = 1,024, 2,560, 3,072, 5,120 and 7,168 within
-//    2% of each other).  A logit is then the sum of two chains, of every other
-//    k-slice, so that the changed order has less rounding and not more.
+//  - A logit is one chain of MFMAs over the k-slices of 32 in ascending order,
+//    as in the tile kernel, whatever workgroup holds its column: equal weight
+//    rows tie exactly, and a row's logits do not depend on the rows beside it.
+//    (K loops that start at another step in each workgroup spread weight rows a
+//    multiple of 4 KB apart over more memory channels: 151,936 columns, 32 rows,
+//    d = 2,048, 106.6 us for 124.5; d = 4,096, 197.9 for 202.6.  They sum equal
+//    rows in different orders, so the greater of two duplicates was a matter of
+//    rounding.)
 //
 // 151,936 columns, d = 5,120, call times on one box against the tile kernels
 // that took these rows before: 9 rows 236 us (6.6 TB/s) against 425; 32 rows
@@ -1787,7 +1789,7 @@ __global__ __launch_bounds__(kLmThreads) void asd_lmhead_kernel(
 // Each K step waits until at most the copies of the later stages are outstanding
 // (they complete in order), then meets the other wavefronts: the step's stage is
 // whole, and the stage before it is read out and takes the next copies.
-template <int kWaves, int kVt, int kRt, int kK, int kStages, bool kSpread>
+template <int kWaves, int kVt, int kRt, int kK, int kStages>
 __global__ __launch_bounds__(64 * kWaves) void asd_lmhead_stream_kernel(
     const unsigned char* __restrict__ hidden, const unsigned char* __restrict__ weight,
     int32_t M, int64_t K, uint32_t share, uint32_t extra, const int32_t* __restrict__ draft_tokens,
@@ -1795,7 +1797,6 @@ __global__ __launch_bounds__(64 * kWaves) void asd_lmhead_stream_kernel(
     static_assert(kK == 64 || kK == 128, "rows of one or two cache lines");
     constexpr int kCols = 16 * kVt * kWaves, kPitch = 2 * kK;
     constexpr int kStageBytes = (kCols + 16 * kRt) * kPitch;
-    constexpr int kChains = kSpread ? 2 : 1;             // accumulators of one logit
     constexpr int kDraftBytes = (16 * kRt + 63) / 64 * 256;
     constexpr int kW = kVt * kK / 32, kH = kRt * kK / 32 / kWaves;   // blocks a wavefront copies
     static_assert(kH * kWaves * 32 == kRt * kK && kStages >= 2, "every wavefront copies alike");
@@ -1831,7 +1832,7 @@ __global__ __launch_bounds__(64 * kWaves) void asd_lmhead_stream_kernel(
     // The next step to copy: of tile `ccol`, byte `ck` of each row.
     int64_t ccol = first;
     u32x4 rw = tile_rsrc(ccol);
-    int ck = kSpread ? (int)(bid % (uint32_t)KT) * kPitch : 0, c_left = KT;
+    int ck = 0;
     auto copy_next = [&](int slot) {
         const uint32_t base = lds0 + slot * kStageBytes;
 #pragma unroll
@@ -1839,9 +1840,9 @@ __global__ __launch_bounds__(64 * kWaves) void asd_lmhead_stream_kernel(
 #pragma unroll
         for (int u = 0; u < kH; ++u)
             lm_lds_copy<false>(rh, vh[u], ck, base + kCols * kPitch + (wave * kH + u) * 1024);
-        ck = ck + kPitch < K2 ? ck + kPitch : 0;
-        if (--c_left == 0) {
-            c_left = KT;
+        ck += kPitch;
+        if (ck == K2) {
+            ck = 0;
             ccol += kCols;
             if (ccol < end) rw = tile_rsrc(ccol);
         }
@@ -1855,13 +1856,11 @@ __global__ __launch_bounds__(64 * kWaves) void asd_lmhead_stream_kernel(
 #pragma unroll
     for (int j = 0; j < kRt; ++j) top[j] = 0; // ranks below every key
     for (int t = 0; t < kStages - 1 && t < steps; ++t) copy_next(t);
-    f32x4 acc[kChains][kVt][kRt];
+    f32x4 acc[kVt][kRt];
 #pragma unroll
-    for (int c = 0; c < kChains; ++c)
+    for (int i = 0; i < kVt; ++i)
 #pragma unroll
-        for (int i = 0; i < kVt; ++i)
-#pragma unroll
-            for (int j = 0; j < kRt; ++j) acc[c][i][j] = (f32x4)(0.0f);
+        for (int j = 0; j < kRt; ++j) acc[i][j] = (f32x4)(0.0f);
     const int offA = (wave * 16 * kVt + lr) * kPitch + ((lq ^ swz(lr)) << 4);
     const int offB = (kCols + lr) * kPitch + ((lq ^ swz(lr)) << 4);
     int slot = 0, k_left = KT;
@@ -1881,8 +1880,8 @@ __global__ __launch_bounds__(64 * kWaves) void asd_lmhead_stream_kernel(
                 const bf16x8 b = *(const bf16x8*)(st + (offB ^ (k * 64)) + j * 16 * kPitch);
 #pragma unroll
                 for (int i = 0; i < kVt; ++i)
-                    acc[k % kChains][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                        a[i], b, acc[k % kChains][i][j], 0, 0, 0);
+                    acc[i][j] =
+                        __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b, acc[i][j], 0, 0, 0);
             }
         }
         slot = slot == kStages - 1 ? 0 : slot + 1;
@@ -1894,11 +1893,10 @@ __global__ __launch_bounds__(64 * kWaves) void asd_lmhead_stream_kernel(
                 for (int i = 0; i < kVt; ++i) {
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
-                        float val = acc[0][i][j][v];
-                        if constexpr (kSpread) val += acc[kChains - 1][i][j][v];
+                        const float val = acc[i][j][v];
                         u[4 * i + v] = __float_as_uint(val);
                     }
-                    acc[0][i][j] = acc[kChains - 1][i][j] = (f32x4)(0.0f);
+                    acc[i][j] = (f32x4)(0.0f);
                 }
                 const bool have = j * 16 + lr < M;
                 const unsigned long long p =
@@ -1938,10 +1936,7 @@ void launch_lmhead_stream(hipStream_t stream, const void* hidden, const void* we
     constexpr int kPerCu = 160 * 1024 / (kStageBytes * kStages + (16 * kRt + 63) / 64 * 256);
     static_assert(kPerCu >= 1, "the ring fits the LDS of a CU");
     const int64_t grid = min((vocab + 63) / 64, (int64_t)num_cus * kPerCu);
-    const bool spread = d % 2048 == 0;
-    auto kernel = spread ? asd_lmhead_stream_kernel<kWaves, kVt, kRt, kK, kStages, true>
-                         : asd_lmhead_stream_kernel<kWaves, kVt, kRt, kK, kStages, false>;
-    kernel<<<(unsigned)grid, 64 * kWaves, 0, stream>>>(
+    asd_lmhead_stream_kernel<kWaves, kVt, kRt, kK, kStages><<<(unsigned)grid, 64 * kWaves, 0, stream>>>(
         (const unsigned char*)hidden, (const unsigned char*)weight, (int32_t)rows, d,
         (uint32_t)(vocab / grid), (uint32_t)(vocab % grid), draft_tokens, best, draft_bits);
 }

@@ -344,6 +344,46 @@ def test_realistic_regime_within_rounding_bound():
     assert np.all(np.abs(g["regret"][:-1] - r_exact) <= 4 * bound[:-1])
 
 
+def _argmax_and_regret(hidden, weight, draft):
+    import torch
+    import paper_2608_03447_amd as asd
+    dev = hidden.device
+    rows = hidden.shape[0]
+    amax = torch.full((rows,), -7, dtype=torch.int32, device=dev)
+    regret = torch.full((rows,), float("nan"), dtype=torch.float32, device=dev)
+    asd.asd_lmhead_verify(
+        hidden, weight, draft, torch.full((1,), rows - 1, dtype=torch.int32, device=dev),
+        torch.full((1,), 1.0, device=dev), torch.full((1,), 1, dtype=torch.int32, device=dev),
+        torch.tensor([[0.0, 0.0]], device=dev), out_argmax=amax, out_regret=regret)
+    torch.cuda.synchronize()
+    return amax.cpu().numpy(), regret.cpu().numpy()
+
+
+@pytest.mark.parametrize("d", [1024, 2048, 4096])
+def test_a_logit_does_not_depend_on_its_column_or_the_batch(d):
+    """Inexact sums.  Every weight row is there twice, 16,500 columns apart: a
+    duplicate of the argmax ties with it, so the lower column is the argmax and
+    the duplicate's regret is zero.  And a row's argmax and regret are the same
+    bits in calls of 9 to 600 rows, through every kernel."""
+    import torch
+    dev = torch.device("cuda:0")
+    half, most = 16500, 600
+    gen = torch.Generator(device=dev).manual_seed(d)
+    hidden = torch.randn((most, d), generator=gen, device=dev).to(torch.bfloat16)
+    weight = torch.randn((half, d), generator=gen, device=dev).to(torch.bfloat16).repeat(2, 1)
+    other = torch.randint(0, 2 * half, (most,), generator=gen, device=dev).to(torch.int32)
+    print("case lmhead duplicates d %d" % d, flush=True)
+    amax, regret = _argmax_and_regret(hidden, weight, other)
+    assert np.all(amax < half)
+    for rows in (9, 16, 24, 32, 64, 100, 128, 129, 256, 300, most):
+        a, r = _argmax_and_regret(hidden[:rows].contiguous(), weight, other[:rows].contiguous())
+        assert np.array_equal(a, amax[:rows]), rows
+        assert np.array_equal(r[:-1].view(np.uint32), regret[:rows - 1].view(np.uint32)), rows
+        twin = torch.from_numpy(amax[:rows] + half).to(dev)
+        a, r = _argmax_and_regret(hidden[:rows].contiguous(), weight, twin)
+        assert np.array_equal(a, amax[:rows]) and np.all(r[:-1] == 0.0), rows
+
+
 def test_explicit_row_offsets_in_any_order():
     """Requests listed in an order other than their rows' (explicit offsets)."""
     from asd_gpu import describe, mismatches
