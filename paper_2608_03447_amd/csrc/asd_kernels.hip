@@ -1374,6 +1374,11 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 #define ASD_LDS __attribute__((address_space(3)))
 
 constexpr int kLmStreamMaxRows = 128;    // fewer rows stream the weights
+// Whole tiles against even shares, over 1 to 128 rows and 1,000 to 151,936
+// columns: 5-7% faster at d = 128 to 1,024 (64 rows of 16,384 columns, d = 256,
+// 11.7 us for 15.5; 33 rows of 40,000, d = 512, 19.9 for 22.8), level from 1,536
+// on, where single calls of a part-full round lose up to 16% (d = 3,072).
+constexpr int kLmStreamShortK = 1024;
 constexpr int kWaitLds = 0xc07f;         // s_waitcnt lgkmcnt(0)
 constexpr int kRsrcWord3 = 0x00020000;   // raw buffer, 32-bit data format
 
@@ -1938,7 +1943,10 @@ __global__ __launch_bounds__(64 * kWaves) void asd_lmhead_stream_kernel(
 }
 
 // As many workgroups as the CUs hold at once (160 KB of LDS each), none with
-// fewer than 64 columns where that can be helped.
+// fewer than 64 columns where that can be helped.  Up to kLmStreamShortK hidden
+// values only as many as whole tiles need: a tile that is part full saves reads,
+// which short K loops do not wait for, and costs its fragments, its ranking and
+// another workgroup's updates of the same rows.
 template <int kWaves, int kVt, int kRt, int kK, int kStages>
 void launch_lmhead_stream(hipStream_t stream, const void* hidden, const void* weight, int64_t rows,
                           int64_t vocab, int64_t d, int num_cus, const int32_t* draft_tokens,
@@ -1946,7 +1954,11 @@ void launch_lmhead_stream(hipStream_t stream, const void* hidden, const void* we
     constexpr int kStageBytes = (16 * kVt * kWaves + 16 * kRt) * 2 * kK;
     constexpr int kPerCu = 160 * 1024 / (kStageBytes * kStages + (16 * kRt + 63) / 64 * 256);
     static_assert(kPerCu >= 1, "the ring fits the LDS of a CU");
-    const int64_t grid = min((vocab + 63) / 64, (int64_t)num_cus * kPerCu);
+    constexpr int kCols = 16 * kVt * kWaves;
+    const int64_t slots = (int64_t)num_cus * kPerCu;
+    const int64_t tiles = (vocab + slots * kCols - 1) / (slots * kCols);     // of a workgroup
+    const int64_t grid = d <= kLmStreamShortK ? (vocab + tiles * kCols - 1) / (tiles * kCols)
+                                              : min((vocab + 63) / 64, slots);
     asd_lmhead_stream_kernel<kWaves, kVt, kRt, kK, kStages><<<(unsigned)grid, 64 * kWaves, 0, stream>>>(
         (const unsigned char*)hidden, (const unsigned char*)weight, (int32_t)rows, d,
         (uint32_t)(vocab / grid), (uint32_t)(vocab % grid), draft_tokens, best, draft_bits);

@@ -142,6 +142,26 @@ def test_weight_stream_shares_bit_exact(rows, vocab, d):
     assert not bad, "differs in %s: %s" % (bad, describe(g, r))
 
 
+@pytest.mark.parametrize("rows,vocab,d", [(16, 32768, 128), (16, 32769, 1024), (16, 32769, 1152),
+                                          (30, 32769, 128), (30, 32769, 1152), (60, 65537, 256),
+                                          (60, 65535, 1152), (90, 32768, 128), (90, 65536, 256),
+                                          (90, 65537, 1024), (90, 65537, 1152)])
+def test_weight_stream_whole_tiles_and_even_shares_bit_exact(rows, vocab, d):
+    """Up to d = 1,024 a workgroup takes whole tiles, above an even share: one
+    column to either side of the vocabularies that fill every workgroup of 256
+    CUs with one and with two tiles (64, 128 or 256 columns)."""
+    from asd_gpu import describe, mismatches
+    rng = np.random.default_rng(rows + vocab + d)
+    hidden, weight, draft = _exact_inputs(rng, rows, vocab, d)
+    lens = [4] * (rows // 5) + [rows % 5 - 1] * (rows % 5 > 0)
+    budget = np.stack([rng.uniform(0, 6, len(lens)), np.zeros(len(lens))], axis=1)
+    print("case lmhead shares rows %d vocab %d d %d" % (rows, vocab, d), flush=True)
+    g = _run(hidden, weight, draft, lens, 1.0, 2, budget)
+    r = oracle.lmhead_verify(hidden, weight, draft, lens, 1.0, 2, budget)
+    bad = mismatches(g, r)
+    assert not bad, "differs in %s: %s" % (bad, describe(g, r))
+
+
 @pytest.mark.parametrize("rows,vocab,d", [(130, 1027, 128), (40, 5000, 256), (300, 640, 128)])
 def test_nonfinite_and_negative_rows_bit_exact(rows, vocab, d):
     """Rows that the epilogue cannot rank by raw patterns: every logit negative,
