@@ -1176,14 +1176,18 @@ hipError_t launch_row(int elem_bytes, dim3 grid, hipStream_t stream, Args... arg
 // the block's end).  A mismatch at position i with r_i <= tau and a following
 // run of at least p greedy drafts (which also gives i + p <= K) counts for
 // (tau, p): with lanes = pairs, the wavefront walks the chunk's mismatches and
-// every lane tests its pair against each.  Counts gather in LDS, then in the
-// caller's uint64 accumulators.
+// every lane tests its pair against each, or, where there are fewer pairs than
+// mismatches, it walks the pairs and every position is tested against each.
+// Counts gather in registers (the first 64 pairs) and LDS, then in the caller's
+// uint64 accumulators.
 //
 // A chain of memory round trips bounds it, so the pairs' thresholds are read
 // with the block lengths.  Workgroups have 16 wavefronts because all of them add
 // to the same few accumulators, one after another.  256 requests of 16 drafts,
 // 35 pairs: 4.4 us a call; with four wavefronts, one ballot per pair and the
-// thresholds read in the loop 7.8 us.
+// thresholds read in the loop 7.8 us.  The shorter walk is for calls of few pairs
+// and many mismatches: 256 requests of 64 drafts that all mismatch, one pair 4.4
+// us, over the mismatches 8.3; of 256 drafts 5.9 and 22.8.
 constexpr int kOppWaves = 16;
 constexpr int kOppMostRequests = 64;     // of one workgroup
 
@@ -1212,6 +1216,35 @@ __global__ __launch_bounds__(64 * kOppWaves) void asd_opportunity_kernel(
     }
     if (tid == 0) s_mism = 0u;
     block_offsets<kOppWaves>(num_requests, block_lens, row_offsets, first, count, s_off);   // + barrier
+
+    // The first 64 pairs, one per lane, and their counts stay in registers.
+    const float t0 = lane < pairs ? s_tau[lane] : 0.0f;
+    const int32_t need0 = lane < pairs ? s_p[lane] : 0;
+    uint32_t n0 = 0;
+    // How many of the mismatches w count for this lane's (t, need): over the
+    // mismatches, or over the pairs of the first `here` lanes.
+    auto walk = [](unsigned long long w, float r, int32_t run, float t, int32_t need) {
+        uint32_t n = 0;
+        for (; w != 0ull; w &= w - 1ull) {
+            const int j = __builtin_ctzll(w);
+            const float rj = __builtin_bit_cast(float, lane_u32(__builtin_bit_cast(uint32_t, r), j));
+            const int32_t run_j = (int32_t)lane_u32((uint32_t)run, j);
+            n += rj <= t && run_j >= need;
+        }
+        return n;
+    };
+    auto walk_shorter = [&](unsigned long long w, float r, int32_t run, float t, int32_t need,
+                            int here) {
+        if (here >= (int)__builtin_popcountll(w)) return walk(w, r, run, t, need);
+        uint32_t n = 0;
+        for (int j = 0; j < here; ++j) {
+            const float tj = __builtin_bit_cast(float, lane_u32(__builtin_bit_cast(uint32_t, t), j));
+            const int32_t need_j = (int32_t)lane_u32((uint32_t)need, j);
+            const unsigned long long q = __ballot(r <= tj && run >= need_j) & w;
+            n = lane == j ? (uint32_t)__builtin_popcountll(q) : n;
+        }
+        return n;
+    };
 
     for (int kq = wave; kq < count; kq += kOppWaves) {            // wave-uniform
         const int32_t K = __builtin_amdgcn_readfirstlane(s_len[kq]);
@@ -1242,19 +1275,16 @@ __global__ __launch_bounds__(64 * kOppWaves) void asd_opportunity_kernel(
                 const unsigned long long mm = __ballot(have && !match);
                 mism_total += (uint32_t)__builtin_popcountll(mm);
                 if (mm) {
-                    for (int k0 = 0; k0 < pairs; k0 += 64) {
-                        const int k = k0 + lane;
+                    n0 += walk_shorter(mm, r, run, t0, need0, min(pairs, 64));
+                    int k = 64 + lane;                // the other pairs: whole groups, the rest
+                    for (; k - lane + 64 <= pairs; k += 64) {
+                        const uint32_t n = walk(mm, r, run, s_tau[k], s_p[k]);
+                        if (n != 0) atomicAdd(&s_counts[k], n);
+                    }
+                    if (k - lane < pairs) {
                         const bool pair = k < pairs;
-                        const float t = pair ? s_tau[k] : 0.0f;
-                        const int32_t need = pair ? s_p[k] : 0;
-                        uint32_t n = 0;
-                        for (unsigned long long w = mm; w != 0ull; w &= w - 1ull) {
-                            const int j = __builtin_ctzll(w);
-                            const float rj = __builtin_bit_cast(
-                                float, lane_u32(__builtin_bit_cast(uint32_t, r), j));
-                            const int32_t run_j = (int32_t)lane_u32((uint32_t)run, j);
-                            n += rj <= t && run_j >= need;
-                        }
+                        const uint32_t n = walk_shorter(mm, r, run, pair ? s_tau[k] : 0.0f,
+                                                        pair ? s_p[k] : 0, pairs - (k - lane));
                         if (pair && n != 0) atomicAdd(&s_counts[k], n);
                     }
                 }
@@ -1265,6 +1295,7 @@ __global__ __launch_bounds__(64 * kOppWaves) void asd_opportunity_kernel(
             if (lane == 0 && mism_total) atomicAdd(&s_mism, mism_total);
         }
     }
+    if (lane < pairs && n0 != 0) atomicAdd(&s_counts[lane], n0);
     __syncthreads();
     for (int k = tid; k < pairs; k += 64 * kOppWaves)
         if (s_counts[k]) atomicAdd(counts + k, (unsigned long long)s_counts[k]);

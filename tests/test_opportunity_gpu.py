@@ -96,6 +96,26 @@ def test_opportunity_explicit_offsets_and_invalid_requests():
     assert m == ref_m and np.array_equal(counts, ref_c)
 
 
+@pytest.mark.parametrize("num_taus,num_ps", [(1, 1), (3, 5), (7, 9), (8, 8), (13, 5), (8, 16)])
+@pytest.mark.parametrize("p_match", [0.0, 0.5, 0.8])
+def test_opportunity_chunks_with_more_mismatches_than_pairs(num_taus, num_ps, p_match):
+    """A 64-position chunk walks its mismatches or the pairs, whichever are fewer:
+    0 to 64 mismatches against groups of 1, 15, 63, 64 and 1 pairs."""
+    rng = np.random.default_rng(num_taus * 100 + num_ps)
+    vocab = 40
+    lens = np.array([1, 2, 15, 16, 17, 62, 63, 64, 65, 66, 127, 128, 129, 300, 1500], np.int32)
+    rows = int(np.sum(lens + 1))
+    y = rng.integers(0, vocab, rows).astype(np.int32)
+    draft = np.where(rng.random(rows) < p_match, y, (y + 1 + rng.integers(0, vocab, rows)) % (vocab + 3))
+    draft = draft.astype(np.int32)
+    regret = rng.choice(np.array([0.0, 0.25, 1.0, 3.0, np.inf, np.nan], np.float32), rows)
+    taus = rng.choice(np.array([-1.0, 0.0, 0.25, 2.0, np.inf, np.nan], np.float32), num_taus)
+    ps = rng.integers(-2, 5, num_ps).astype(np.int32)
+    counts, m = gpu_counts(draft, y, regret, vocab, lens, taus, ps)
+    ref_c, ref_m = oracle.opportunity(draft, y, regret, vocab, lens, taus, ps)
+    assert m == ref_m and np.array_equal(counts, ref_c)
+
+
 @pytest.mark.parametrize("num_taus,num_ps", [(1, 1), (8, 8), (13, 5), (32, 32), (1, 1024)])
 @pytest.mark.parametrize("num_requests", [15, 16, 17, 33])
 def test_opportunity_pair_and_request_counts_around_a_workgroup(num_taus, num_ps, num_requests):
