@@ -180,6 +180,24 @@ def asd_workspace_bytes(dtype, vocab, num_requests, total_rows) -> int:
     return int(_load().asd_workspace_bytes(code, int(vocab), int(num_requests), int(total_rows)))
 
 
+class _AsItIs:
+    def __enter__(self):
+        pass
+
+    def __exit__(self, *exc):
+        pass
+
+
+_AS_IT_IS = _AsItIs()
+
+
+def _on(dev):
+    """A context with ``dev`` as the current device; nothing to enter where it is already."""
+    if dev.index is not None and dev.index == torch.cuda.current_device():
+        return _AS_IT_IS
+    return torch.cuda.device(dev)
+
+
 def _per_request(value, n, dtype, device, name):
     if isinstance(value, torch.Tensor):
         if value.dtype != dtype or value.device != device or value.shape != (n,):
@@ -222,26 +240,21 @@ def _marshal(dev, rows, draft_tokens, block_lens, tau, exc_cap, budget, row_offs
     exc_cap = _per_request(exc_cap, n, torch.int32, dev, "exc_cap")
     block_lens = block_lens.contiguous()
     draft_tokens = draft_tokens.contiguous()
+    _check_vector(out_accept_len, n, torch.int32, dev, "out_accept_len")
+    _check_vector(out_next_token, n, torch.int32, dev, "out_next_token")
+    _check_vector(out_argmax, rows, torch.int32, dev, "out_argmax")
+    _check_vector(out_regret, rows, torch.float32, dev, "out_regret")
     if out_accept_len is None:
         out_accept_len = torch.empty(n, dtype=torch.int32, device=dev)
     if out_next_token is None:
         out_next_token = torch.empty(n, dtype=torch.int32, device=dev)
-    for t, name, shape, dt in ((out_accept_len, "out_accept_len", (n,), torch.int32),
-                               (out_next_token, "out_next_token", (n,), torch.int32),
-                               (out_argmax, "out_argmax", (rows,), torch.int32),
-                               (out_regret, "out_regret", (rows,), torch.float32)):
-        if t is not None and (t.dtype != dt or t.shape != shape or t.device != dev
-                              or not t.is_contiguous()):
-            raise ValueError("%s must be a contiguous %s tensor of shape %s on %s"
-                             % (name, dt, shape, dev))
 
-    def p(t):
-        return None if t is None else ctypes.c_void_p(t.data_ptr())
-
-    stream = torch.cuda.current_stream(dev).cuda_stream
-    args = [n, rows, p(draft_tokens), p(block_lens), p(row_offsets), p(tau), p(exc_cap),
-            p(budget), p(out_accept_len), p(out_next_token), p(out_argmax), p(out_regret),
-            ctypes.c_void_p(stream)]
+    stream = torch.cuda.current_stream(dev.index).cuda_stream
+    args = [n, rows, draft_tokens.data_ptr(), block_lens.data_ptr(),
+            None if row_offsets is None else row_offsets.data_ptr(), tau.data_ptr(),
+            exc_cap.data_ptr(), budget.data_ptr(), out_accept_len.data_ptr(),
+            out_next_token.data_ptr(), None if out_argmax is None else out_argmax.data_ptr(),
+            None if out_regret is None else out_regret.data_ptr(), stream]
     keep = (tau, exc_cap, block_lens, draft_tokens)
     return args, out_accept_len, out_next_token, keep
 
@@ -265,11 +278,11 @@ def asd_verify(logits, draft_tokens, block_lens, tau, exc_cap, budget, *, row_of
     if r is not None:
         return _result(r, "asd_verify")
     _check_logits(logits)
-    with torch.cuda.device(logits.device):
+    with _on(logits.device):
         args, acc, nxt, keep = _marshal(logits.device, logits.shape[0], draft_tokens, block_lens,
                                         tau, exc_cap, budget, row_offsets, out_accept_len,
                                         out_next_token, out_argmax, out_regret)
-        st = _load().asd_verify(ctypes.c_void_p(logits.data_ptr()), _DTYPES[logits.dtype],
+        st = _load().asd_verify(logits.data_ptr(), _DTYPES[logits.dtype],
                                 logits.shape[1], *args)
     del keep
     if st != 0:
@@ -289,11 +302,11 @@ def asd_verify_static(logits, draft_tokens, block_lens, tau, exc_cap, budget, *,
     if r is not None:
         return _result(r, "asd_verify_static")
     _check_logits(logits)
-    with torch.cuda.device(logits.device):
+    with _on(logits.device):
         args, acc, nxt, keep = _marshal(logits.device, logits.shape[0], draft_tokens, block_lens,
                                         tau, exc_cap, budget, row_offsets, out_accept_len,
                                         out_next_token, out_argmax, out_regret)
-        st = _load().asd_verify_static(ctypes.c_void_p(logits.data_ptr()),
+        st = _load().asd_verify_static(logits.data_ptr(),
                                        _DTYPES[logits.dtype], logits.shape[1], *args)
     del keep
     if st != 0:
@@ -308,13 +321,13 @@ def asd_verify_ws(logits, draft_tokens, block_lens, tau, exc_cap, budget, worksp
     if workspace.dtype != torch.uint8 or not workspace.is_contiguous():
         raise ValueError("workspace must be a contiguous uint8 tensor")
     _check_logits(logits)
-    with torch.cuda.device(logits.device):
+    with _on(logits.device):
         args, acc, nxt, keep = _marshal(logits.device, logits.shape[0], draft_tokens, block_lens,
                                         tau, exc_cap, budget, row_offsets, out_accept_len,
                                         out_next_token, out_argmax, out_regret)
-        st = _load().asd_verify_ws(ctypes.c_void_p(logits.data_ptr()), _DTYPES[logits.dtype],
+        st = _load().asd_verify_ws(logits.data_ptr(), _DTYPES[logits.dtype],
                                    logits.shape[1], *args,
-                                   ctypes.c_void_p(workspace.data_ptr()), workspace.numel())
+                                   workspace.data_ptr(), workspace.numel())
     del keep
     if st != 0:
         raise AsdError(st, "asd_verify_ws")
@@ -335,13 +348,13 @@ def asd_verify_ex(logits, draft_tokens, block_lens, tau, exc_cap, budget, *, fla
     if workspace is not None and (workspace.dtype != torch.uint8 or not workspace.is_contiguous()):
         raise ValueError("workspace must be a contiguous uint8 tensor")
     _check_logits(logits)
-    with torch.cuda.device(logits.device):
+    with _on(logits.device):
         args, acc, nxt, keep = _marshal(logits.device, logits.shape[0], draft_tokens, block_lens,
                                         tau, exc_cap, budget, row_offsets, out_accept_len,
                                         out_next_token, out_argmax, out_regret)
-        ws = None if workspace is None else ctypes.c_void_p(workspace.data_ptr())
+        ws = None if workspace is None else workspace.data_ptr()
         ws_bytes = 0 if workspace is None else workspace.numel()
-        st = _load().asd_verify_ex(ctypes.c_void_p(logits.data_ptr()), _DTYPES[logits.dtype],
+        st = _load().asd_verify_ex(logits.data_ptr(), _DTYPES[logits.dtype],
                                    logits.shape[1], *args[:-1], int(flags), args[-1], ws,
                                    ws_bytes)
     del keep
@@ -356,10 +369,9 @@ def asd_device_error(clear=False, device=None) -> int:
     dev = torch.device("cuda", torch.cuda.current_device()) if device is None \
         else torch.device(device)
     word = ctypes.c_uint32(0)
-    with torch.cuda.device(dev):
+    with _on(dev):
         stream = torch.cuda.current_stream(dev).cuda_stream
-        st = _load().asd_device_error(ctypes.byref(word), 1 if clear else 0,
-                                      ctypes.c_void_p(stream))
+        st = _load().asd_device_error(ctypes.byref(word), 1 if clear else 0, stream)
     if st != 0:
         raise AsdError(st, "asd_device_error")
     return int(word.value)
@@ -389,7 +401,7 @@ def asd_row_pass(logits, draft_tokens, out_partials=None):
     if draft_tokens.dtype != torch.int32 or draft_tokens.shape != (rows,) \
             or draft_tokens.device != dev:
         raise ValueError("draft_tokens must be int32 of shape (%d,) on %s" % (rows, dev))
-    with torch.cuda.device(dev):
+    with _on(dev):
         splits = asd_row_splits(logits.dtype, vocab, rows)
         if splits < 1:
             raise ValueError("no row pass for %d rows of %d columns" % (rows, vocab))
@@ -401,9 +413,8 @@ def asd_row_pass(logits, draft_tokens, out_partials=None):
                              % (rows, splits, dev))
         draft_tokens = draft_tokens.contiguous()
         stream = torch.cuda.current_stream(dev).cuda_stream
-        st = _load().asd_row_pass(ctypes.c_void_p(logits.data_ptr()), _DTYPES[logits.dtype],
-                                  vocab, rows, ctypes.c_void_p(draft_tokens.data_ptr()),
-                                  ctypes.c_void_p(out_partials.data_ptr()), ctypes.c_void_p(stream))
+        st = _load().asd_row_pass(logits.data_ptr(), _DTYPES[logits.dtype], vocab, rows,
+                                  draft_tokens.data_ptr(), out_partials.data_ptr(), stream)
     if st != 0:
         raise AsdError(st, "asd_row_pass")
     return out_partials
@@ -418,10 +429,10 @@ def asd_read_probe(buf, rows, row_bytes, out_word):
         raise ValueError("buf must be a contiguous GPU tensor of at least rows * row_bytes bytes")
     if out_word.dtype != torch.int32 or out_word.numel() < 1 or out_word.device != buf.device:
         raise ValueError("out_word must be an int32 tensor on the buffer's device")
-    with torch.cuda.device(buf.device):
+    with _on(buf.device):
         stream = torch.cuda.current_stream(buf.device).cuda_stream
-        st = _load().asd_read_probe(ctypes.c_void_p(buf.data_ptr()), int(rows), int(row_bytes),
-                                    ctypes.c_void_p(out_word.data_ptr()), ctypes.c_void_p(stream))
+        st = _load().asd_read_probe(buf.data_ptr(), int(rows), int(row_bytes), out_word.data_ptr(),
+                                    stream)
     if st != 0:
         raise AsdError(st, "asd_read_probe")
 
@@ -435,11 +446,10 @@ def asd_mfma_probe(operands, workgroups, steps, out):
         raise ValueError("operands must be a contiguous bfloat16 GPU tensor")
     if out.dtype != torch.int32 or out.numel() < workgroups or out.device != operands.device:
         raise ValueError("out must be an int32 tensor of at least `workgroups` entries")
-    with torch.cuda.device(operands.device):
+    with _on(operands.device):
         stream = torch.cuda.current_stream(operands.device).cuda_stream
-        st = _load().asd_mfma_probe(ctypes.c_void_p(operands.data_ptr()), operands.numel() // 8,
-                                    int(workgroups), int(steps), ctypes.c_void_p(out.data_ptr()),
-                                    ctypes.c_void_p(stream))
+        st = _load().asd_mfma_probe(operands.data_ptr(), operands.numel() // 8, int(workgroups),
+                                    int(steps), out.data_ptr(), stream)
     if st != 0:
         raise AsdError(st, "asd_mfma_probe")
 
@@ -473,13 +483,11 @@ def asd_shard_argmax(shard_logits, vocab_offset, vocab, draft_tokens, out_partia
             or not out_partials.is_contiguous() or out_partials.device != dev:
         raise ValueError("out_partials must be a contiguous int32 (%d, 4) tensor on %s" % (rows, dev))
     draft_tokens = draft_tokens.contiguous()
-    with torch.cuda.device(dev):
+    with _on(dev):
         stream = torch.cuda.current_stream(dev).cuda_stream
-        st = _load().asd_shard_argmax(ctypes.c_void_p(shard_logits.data_ptr()),
-                                      _DTYPES[shard_logits.dtype], width, int(vocab_offset),
-                                      int(vocab), rows, ctypes.c_void_p(draft_tokens.data_ptr()),
-                                      ctypes.c_void_p(out_partials.data_ptr()),
-                                      ctypes.c_void_p(stream))
+        st = _load().asd_shard_argmax(shard_logits.data_ptr(), _DTYPES[shard_logits.dtype], width,
+                                      int(vocab_offset), int(vocab), rows,
+                                      draft_tokens.data_ptr(), out_partials.data_ptr(), stream)
     if st != 0:
         raise AsdError(st, "asd_shard_argmax")
     return out_partials
@@ -506,11 +514,11 @@ def asd_verify_partials(partials, shard_vocab, vocab, draft_tokens, block_lens, 
         raise ValueError("partials must be a contiguous int32 (num_shards, total_rows, 4) GPU tensor")
     dev = partials.device
     shards, rows = partials.shape[0], partials.shape[1]
-    with torch.cuda.device(dev):
+    with _on(dev):
         args, acc, nxt, keep = _marshal(dev, rows, draft_tokens, block_lens, tau, exc_cap, budget,
                                         row_offsets, out_accept_len, out_next_token,
                                         out_argmax, out_regret)
-        st = _load().asd_verify_partials(ctypes.c_void_p(partials.data_ptr()), shards,
+        st = _load().asd_verify_partials(partials.data_ptr(), shards,
                                          int(shard_vocab), int(vocab), *args)
     del keep
     if st != 0:
@@ -554,14 +562,14 @@ def asd_opportunity(draft_tokens, row_argmax, row_regret, vocab, block_lens, tau
     block_lens = block_lens.contiguous()
 
     def p(t):
-        return None if t is None else ctypes.c_void_p(t.data_ptr())
+        return None if t is None else t.data_ptr()
 
-    with torch.cuda.device(dev):
+    with _on(dev):
         st = _load().asd_opportunity(p(draft_tokens), p(row_argmax), p(row_regret), int(vocab), n,
                                      rows, p(block_lens), p(row_offsets), p(taus),
                                      taus.shape[0], p(ps), ps.shape[0], p(counts),
                                      p(mismatches),
-                                     ctypes.c_void_p(torch.cuda.current_stream(dev).cuda_stream))
+                                     torch.cuda.current_stream(dev).cuda_stream)
     if st != 0:
         raise AsdError(st, "asd_opportunity")
 
@@ -590,13 +598,13 @@ def asd_commit(draft_tokens, block_lens, accept_len, next_token, tokens, seq_len
     _check_vector(row_offsets, n, torch.int64, dev, "row_offsets")
 
     def p(t):
-        return None if t is None else ctypes.c_void_p(t.data_ptr())
+        return None if t is None else t.data_ptr()
 
-    with torch.cuda.device(dev):
+    with _on(dev):
         st = _load().asd_commit(p(draft_tokens), p(block_lens), p(row_offsets), n,
                                 draft_tokens.shape[0], p(accept_len), p(next_token), p(tokens),
                                 tokens.shape[1], p(seq_len), p(out_committed),
-                                ctypes.c_void_p(torch.cuda.current_stream(dev).cuda_stream))
+                                torch.cuda.current_stream(dev).cuda_stream)
     if st != 0:
         raise AsdError(st, "asd_commit")
 
@@ -630,13 +638,13 @@ def asd_verify_commit(logits, draft_tokens, block_lens, tau, exc_cap, budget, to
     if workspace is not None and (workspace.dtype != torch.uint8 or not workspace.is_contiguous()
                                   or workspace.device != dev):
         raise ValueError("workspace must be a contiguous uint8 tensor on %s" % dev)
-    with torch.cuda.device(dev):
+    with _on(dev):
         args, acc, nxt, keep = _marshal(dev, logits.shape[0], draft_tokens, block_lens, tau,
                                         exc_cap, budget, row_offsets, out_accept_len,
                                         out_next_token, out_argmax, out_regret)
-        p = (lambda t: None if t is None else ctypes.c_void_p(t.data_ptr()))
+        p = (lambda t: None if t is None else t.data_ptr())
         st = _load().asd_verify_commit(
-            ctypes.c_void_p(logits.data_ptr()), _DTYPES[logits.dtype], logits.shape[1],
+            logits.data_ptr(), _DTYPES[logits.dtype], logits.shape[1],
             *args[:-1], p(tokens), tokens.shape[1], p(seq_len), p(out_committed), args[-1],
             p(workspace), 0 if workspace is None else workspace.numel())
     del keep
@@ -663,12 +671,11 @@ def asd_lmhead_verify(hidden, weight, draft_tokens, block_lens, tau, exc_cap, bu
     if hidden.shape[1] != weight.shape[1] or hidden.device != weight.device:
         raise ValueError("hidden and weight must share d and device")
     dev = hidden.device
-    with torch.cuda.device(dev):
+    with _on(dev):
         args, acc, nxt, keep = _marshal(dev, hidden.shape[0], draft_tokens, block_lens, tau,
                                         exc_cap, budget, row_offsets, out_accept_len,
                                         out_next_token, out_argmax, out_regret)
-        st = _load().asd_lmhead_verify(ctypes.c_void_p(hidden.data_ptr()),
-                                       ctypes.c_void_p(weight.data_ptr()), hidden.shape[1],
+        st = _load().asd_lmhead_verify(hidden.data_ptr(), weight.data_ptr(), hidden.shape[1],
                                        weight.shape[0], *args)
     del keep
     if st != 0:
