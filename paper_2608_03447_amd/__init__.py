@@ -9,17 +9,19 @@ fails, an exception is raised.
 The per-round calls first try ``_asd_binding``, which does the same marshalling
 in native code for the ordinary arguments (tensors on the current device, dense,
 of the right types and shapes) and declines any others; the Python code below it
-then converts what it accepts and raises what it refuses.
+then converts what it accepts and raises what it refuses.  Without a binding built
+from these sources for this torch, the Python code takes every call.
 """
 import ctypes
 import functools
 import importlib
 import os
 import types
+import warnings
 
 import torch
 
-from .build import BINDING, BINDING_SOURCES, HASHED_SOURCES, LIBRARY, source_hash
+from .build import BINDING, HASHED_SOURCES, LIBRARY, binding_hash, source_hash
 
 __all__ = ["asd_verify", "asd_verify_static", "asd_verify_ws", "asd_verify_ex", "asd_shard_argmax",
            "asd_verify_partials", "asd_opportunity", "asd_commit", "asd_verify_commit",
@@ -127,17 +129,44 @@ def _load():
     return lib
 
 
+def _load_binding():
+    """The native marshalling module; RuntimeError unless it was built from these
+    sources for the torch that runs."""
+    if not os.path.exists(BINDING):
+        raise RuntimeError("%s is not built; run __graft_entry__.build()" % BINDING)
+    try:
+        binding = importlib.import_module("._asd_binding", __name__)
+    except ImportError as e:
+        raise RuntimeError("%s does not load (%s); run __graft_entry__.build()" % (BINDING, e)) from e
+    built, current = binding.source_hash(), binding_hash()
+    if built != current:
+        raise RuntimeError("%s was built from other sources or for another torch (built %s, now %s); "
+                           "run __graft_entry__.build()" % (BINDING, built, current))
+    return binding
+
+
+class _NoBinding:
+    """In the place of the binding's functions: declines every call."""
+
+    def __getattr__(self, name):
+        return self._decline
+
+    @staticmethod
+    def _decline(*args):
+        return None
+
+
 def _load_fast():
     """The native marshalling (``_asd_binding``), bound to the library's entry points."""
     global _fast
     lib = _load()
-    if not os.path.exists(BINDING):
-        raise RuntimeError("%s is not built; run __graft_entry__.build() first" % BINDING)
-    binding = importlib.import_module("._asd_binding", __name__)
-    built, current = binding.source_hash(), source_hash(BINDING_SOURCES)
-    if built != current:
-        raise RuntimeError("%s was built from other sources (built %s, sources %s); run "
-                           "__graft_entry__.build() again" % (BINDING, built, current))
+    try:
+        binding = _load_binding()
+    except (RuntimeError, OSError) as e:
+        warnings.warn("%s; the Python marshalling takes the calls, at about 10 us more each" % e,
+                      RuntimeWarning, stacklevel=3)
+        _fast = _NoBinding()
+        return _fast
 
     def bind(function, entry):
         return functools.partial(function, ctypes.cast(getattr(lib, entry), ctypes.c_void_p).value)

@@ -12,6 +12,7 @@ import hashlib
 import os
 import re
 import subprocess
+import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -57,6 +58,15 @@ def build_library(verbose: bool = False, output: str = LIBRARY, extra_flags=()) 
     return output
 
 
+def binding_hash() -> str:
+    """Of the binding's sources and of the torch and Python whose layouts it is compiled for."""
+    import torch
+
+    built_for = "%s %s %d %s" % (source_hash(BINDING_SOURCES), torch.__version__,
+                                 torch._C._GLIBCXX_USE_CXX11_ABI, sys.implementation.cache_tag)
+    return hashlib.sha256(built_for.encode()).hexdigest()[:16]
+
+
 def build_binding(verbose: bool = False, output: str = BINDING) -> str:
     """The native marshalling, against the installed torch (host code only)."""
     import sysconfig
@@ -69,7 +79,7 @@ def build_binding(verbose: bool = False, output: str = BINDING) -> str:
                "/opt/rocm/include", sysconfig.get_paths()["include"]]
     cmd = ["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1",
            "-DUSE_ROCM", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
-           '-DASD_BINDING_HASH="%s"' % source_hash(BINDING_SOURCES)]
+           '-DASD_BINDING_HASH="%s"' % binding_hash()]
     for path in include:
         cmd += ["-isystem", path]
     cmd += [BINDING_SOURCES[0], "-o", output + ".tmp", "-L" + os.path.join(base, "lib"), "-lc10",

@@ -98,6 +98,16 @@ def test_native_calls_equal_python_calls(call, dtype, monkeypatch):
         assert np.array_equal(a, b)
 
 
+def test_calls_run_without_a_binding(monkeypatch):
+    native = _outputs(_state(), "verify")
+    monkeypatch.setattr(asd, "_fast", None)
+    monkeypatch.setattr(asd, "BINDING", asd.BINDING + ".missing")
+    with pytest.warns(RuntimeWarning, match="Python marshalling"):
+        python = _outputs(_state(), "verify")
+    for a, b in zip(native, python):
+        assert np.array_equal(a, b)
+
+
 CHANGES = {
     "scalar controls": lambda s: setattr(s, "tau", 2.0) or setattr(s, "cap", 1),
     "strided drafts": lambda s: setattr(s, "draft", s.draft.repeat_interleave(2)[::2]),
