@@ -2000,9 +2000,11 @@ void launch_lmhead_tiles(int64_t grid, hipStream_t stream, const void* hidden, c
                          int64_t rows, int64_t vocab, int64_t d, int64_t tiles_m, int64_t tiles,
                          int64_t group, const int32_t* draft_tokens, unsigned long long* best,
                          uint32_t* draft_bits) {
-    auto kernel = tiles_m <= kLmOnceMaxRowTiles ? asd_lmhead_kernel<kNr, kLmheadGroupFew, true>
-                  : group == kLmheadGroupFew    ? asd_lmhead_kernel<kNr, kLmheadGroupFew, false>
-                                                : asd_lmhead_kernel<kNr, kLmheadGroup, false>;
+    auto kernel = asd_lmhead_kernel<kNr, kLmheadGroupFew, true>;
+    if constexpr (kNr >= lmhead_least_height(kLmOnceMaxRowTiles + 1))
+        if (tiles_m > kLmOnceMaxRowTiles) kernel = asd_lmhead_kernel<kNr, kLmheadGroupFew, false>;
+    if constexpr (kNr >= lmhead_least_height(kLmheadFewRowTiles + 1))
+        if (group == kLmheadGroup) kernel = asd_lmhead_kernel<kNr, kLmheadGroup, false>;
     kernel<<<(unsigned)grid, kLmThreads, 0, stream>>>(
         (const unsigned char*)hidden, (const unsigned char*)weight, rows, vocab, d, (uint32_t)tiles_m,
         (uint32_t)tiles, draft_tokens, best, draft_bits);
@@ -2267,16 +2269,13 @@ hipError_t launch_lmhead_verify(const void* hidden, const void* weight, int64_t 
         const int64_t tiles =
             tiles_m * group * (((vocab + kLmCols - 1) / kLmCols + group - 1) / group);
         const int64_t grid = (tiles + 7) / 8 * 8;
-        // A row tile's height: the rows spread evenly, in steps of 32.  More
-        // than 128 rows leave it above 128.
-        const int64_t nr = ((rows + tiles_m - 1) / tiles_m + 31) / 32;
-        auto launch = nr <= 5   ? launch_lmhead_tiles<5>
+        const int64_t nr = lmhead_tile_height(rows);
+        auto launch = nr == 5   ? launch_lmhead_tiles<5>
                       : nr == 6 ? launch_lmhead_tiles<6>
                       : nr == 7 ? launch_lmhead_tiles<7>
                                 : launch_lmhead_tiles<8>;
         launch(grid, stream, hidden, weight, rows, vocab, d, tiles_m, tiles, group,
-               a.draft_tokens, best,
-               draft_bits);
+               a.draft_tokens, best, draft_bits);
     }
     if ((err = hipGetLastError()) != hipSuccess) return err;
     ScanArgs A = scan_args(a, rows, vocab, 2);

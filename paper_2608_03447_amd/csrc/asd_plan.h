@@ -177,7 +177,17 @@ constexpr int kLmheadGroup = 4;
 // 1,148; 1,275 rows of 32,000 columns, d = 4,096, 263 -> 262), while 17 row tiles
 // want four (4,352 rows 4,772 us, in twos 4,881).
 constexpr int kLmheadGroupFew = 2, kLmheadFewRowTiles = 5;
-inline int64_t lmhead_row_tiles(int64_t rows) { return (rows + 255) / 256; }
+constexpr int64_t lmhead_row_tiles(int64_t rows) { return (rows + 255) / 256; }
+// A row tile's height in steps of 32 rows: the rows spread evenly over the row
+// tiles (above 128 rows, 5 to 8 steps).
+constexpr int64_t lmhead_tile_height(int64_t rows) {
+    return ((rows + lmhead_row_tiles(rows) - 1) / lmhead_row_tiles(rows) + 31) / 32;
+}
+// The least height of any call of at least this many row tiles (that of its
+// fewest rows, which grows with the tiles): lower ones need no kernel of theirs.
+constexpr int64_t lmhead_least_height(int64_t row_tiles) {
+    return lmhead_tile_height(256 * (row_tiles - 1) + 1);
+}
 hipError_t launch_lmhead_verify(const void* hidden, const void* weight, int64_t d,
                                 int64_t vocab, int64_t rows, const CallArgs& a, void* workspace,
                                 int num_cus, hipStream_t stream);
