@@ -82,13 +82,18 @@ def test_random_split_plan_calls_match_the_oracle(block):
     _run_block(np.random.default_rng(7000 + block), "fuzz-split %d" % block, large_vocab=True)
 
 
-def _run_block(rng, name, large_vocab, max_requests=None, caller_workspace=False, cases=25):
+def _run_block(rng, name, large_vocab, max_requests=None, caller_workspace=False, cases=25,
+               wanted=None):
     """`cases` random calls against the oracle.  With `caller_workspace` every
     call gets a workspace of its own (so the two-launch form runs); otherwise
-    the library's, where small calls run as one launch."""
+    the library's, where small calls run as one launch.  `wanted(dtype, vocab,
+    rows)`, if given, says which draws to run."""
     for case in range(cases):
-        dtype, logits, draft, lens, offsets, tau, cap, budget, raw_gate = _case(
-            rng, large_vocab, max_requests)
+        while True:
+            dtype, logits, draft, lens, offsets, tau, cap, budget, raw_gate = _case(
+                rng, large_vocab, max_requests)
+            if wanted is None or wanted(dtype, logits.shape[1], logits.shape[0]):
+                break
         rows, vocab = logits.shape
         n = len(lens)
         label = "%s.%d: %s rows %d vocab %d requests %d offsets %s raw_gate %s" % (

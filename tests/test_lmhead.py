@@ -277,10 +277,35 @@ def _run_device(hidden, weight, draft, w, budget):
             "budget": tb.cpu().numpy()}
 
 
+@pytest.mark.parametrize("rows", [129, 256])
+def test_maximum_hidden_size_in_the_tile_kernel_bit_exact(rows):
+    """d = 2^20 in tiles of 160 and 256 rows: the copies reach their largest
+    offsets (255 rows of 2 MB in both operands), the three weight stages turn over
+    through 16,384 steps of 64, and a second weight tile holds one column."""
+    import torch
+    from asd_gpu import describe, mismatches
+    vocab, d = 257, 1 << 20
+    gen = torch.Generator().manual_seed(rows)
+
+    def draw(n, scale):
+        t = torch.randint(-2, 3, (n, d), generator=gen, dtype=torch.int8).to(torch.bfloat16) * scale
+        return t.view(torch.int16).numpy().view(np.uint16)
+    hidden, weight = draw(rows, 1.0), draw(vocab, 0.5)
+    z = oracle.lmhead_logits(hidden, weight)
+    assert np.abs(z).max() < 2.0 ** 22        # and every partial sum a multiple of 1/2: exact
+    draft = np.where(np.arange(rows) % 3, np.argmax(z, axis=1), vocab - 1).astype(np.int32)
+    print("case lmhead rows %d vocab %d d %d" % (rows, vocab, d), flush=True)
+    g = _run(hidden, weight, draft, [rows - 1], 1.0, 2, [[4.0, 0.0]])
+    r = oracle.verify(z, draft, [rows - 1], 1.0, 2, [[4.0, 0.0]])
+    bad = mismatches(g, r)
+    assert not bad, "differs in %s: %s" % (bad, describe(g, r))
+
+
 def test_maximum_hidden_size_bit_exact():
-    """d = 2^20, the largest hidden size the call accepts: the copies reach
-    their largest offsets (255 rows of 2 MB) and the K loop runs 16,384
-    steps.  Exact regime: every partial sum is a multiple of 1/2 below 2^22."""
+    """d = 2^20, the largest hidden size the call accepts, in the weight stream:
+    the copies reach their largest offsets there (63 rows of 2 MB) and a K loop
+    runs 8,192 steps of 128.  Exact regime: every partial sum is a multiple of
+    1/2 below 2^22."""
     from asd_gpu import describe, mismatches
     rng = np.random.default_rng(20)
     rows, vocab, d = 4, 257, 1 << 20
@@ -362,6 +387,33 @@ def test_realistic_regime_within_rounding_bound():
     assert np.all(z.max(axis=1) - exact_at_gpu <= 2 * bound)
     r_exact = z.max(axis=1)[:-1] - z[np.arange(rows - 1), draft[:-1]]
     assert np.all(np.abs(g["regret"][:-1] - r_exact) <= 4 * bound[:-1])
+
+
+@pytest.mark.parametrize("d", [1024, 2048, 4096])
+@pytest.mark.parametrize("rows", [9, 24, 64, 100, 120, 300])
+def test_inexact_sums_of_every_kernel_within_rounding_bound(rows, d):
+    """The bound of the realistic regime over the row counts that take kernels of
+    their own (100 rows of a vocabulary of one narrow tile per CU, 120 of a larger
+    one): argmax where the top two are further apart, and every regret."""
+    rng = np.random.default_rng(rows + d)
+    vocab = 33000 if rows == 120 else 3000
+    hidden = W.f32_to_bf16(rng.standard_normal((rows, d), dtype=np.float32))
+    weight = W.f32_to_bf16(rng.standard_normal((vocab, d), dtype=np.float32) * np.float32(d ** -0.5))
+    draft = rng.integers(0, vocab, rows).astype(np.int32)
+    print("case lmhead inexact rows %d vocab %d d %d" % (rows, vocab, d), flush=True)
+    g = _run(hidden, weight, draft, [rows - 1], 1.0, 1, [[1.0, 0.0]])
+    h64 = W.bf16_to_f32(hidden).astype(np.float64)
+    w64 = W.bf16_to_f32(weight).astype(np.float64)
+    z = h64 @ w64.T
+    bound = 2.0 * d * 2.0 ** -24 * (np.abs(h64) @ np.abs(w64).T).max(axis=1)
+    top = np.sort(z, axis=1)[:, -2:]
+    decided = top[:, 1] - top[:, 0] > 2 * bound
+    assert decided.mean() > 0.5
+    assert np.array_equal(g["argmax"][decided], np.argmax(z, axis=1)[decided])
+    assert np.all(top[:, 1] - z[np.arange(rows), g["argmax"]] <= 2 * bound)
+    exact = top[:-1, 1] - z[np.arange(rows - 1), draft[:-1]]
+    wrong = draft[:-1] != g["argmax"][:-1]
+    assert np.all(np.abs(g["regret"][:-1] - exact)[wrong] <= 4 * bound[:-1][wrong])
 
 
 def _argmax_and_regret(hidden, weight, draft):

@@ -22,13 +22,24 @@ DEV = torch.device("cuda:0")
     (0, False, False), (1, False, False), (2, True, False), (3, True, False),
     (0, False, True), (2, True, True)])
 def test_random_small_calls_match_the_oracle(block, large_vocab, caller):
-    """At most eight requests: with the library workspace most of these calls
-    take the single launch (with whole rows or split rows, commit or not, raw
-    gate, explicit offsets, special values); with a caller workspace the same
-    calls take two launches."""
+    """At most eight requests: with the library workspace the calls of up to 96
+    tiles take the single launch (most calls on whole rows, under half of those on
+    split rows; commit or not, raw gate, explicit offsets, special values); with a
+    caller workspace the same calls take two launches."""
     _run_block(np.random.default_rng(9000 + block), "small %d%s" % (block, " caller" if caller
                                                                      else ""),
                large_vocab, max_requests=8, caller_workspace=caller, cases=40)
+
+
+@pytest.mark.parametrize("block", range(3))
+def test_random_single_launch_calls_on_split_rows_match_the_oracle(block):
+    """Split rows and at most 96 tiles, so that every call takes the single
+    launch and its last tile combines the partials that other tiles wrote."""
+    def one_launch(dtype, vocab, rows):
+        splits = asd.asd_row_splits(torch.bfloat16 if dtype == "bf16" else torch.float32, vocab, rows)
+        return splits > 1 and rows * splits <= 96
+    _run_block(np.random.default_rng(9100 + block), "split rows %d" % block, True, max_requests=3,
+               cases=30, wanted=one_launch)
 
 
 def _workload1_tensors():
