@@ -1429,19 +1429,19 @@ __device__ __forceinline__ void lm_lds_copy(u32x4 rsrc, int voff, int k0b, uint3
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
                      :
                      : "s"(lds), "v"(voff), "s"(rsrc), "s"(k0b)
-                     : "m0", "memory");
+                     : "memory");
     else
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                      :
                      : "s"(lds), "v"(voff), "s"(rsrc), "s"(k0b)
-                     : "m0", "memory");
+                     : "memory");
 }
 
 __device__ __forceinline__ void lm_lds_copy_dword(u32x4 rsrc, int voff, uint32_t lds) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dword %1, %2, 0 offen lds"
                  :
                  : "s"(lds), "v"(voff), "s"(rsrc)
-                 : "m0", "memory");
+                 : "memory");
 }
 
 template <int kOutstanding>
