@@ -1422,7 +1422,9 @@ __device__ __forceinline__ int lm_swz(int r) { return (r >> 1) & 7; }
 // Global -> LDS copies are written in asm: they fill LDS and no registers, and
 // the compiler, which cannot tell a ring's stages apart, would wait for all of
 // them before any fragment read.  The wait states before a copy cover a resource
-// or LDS address that has just been written.
+// or LDS address that has just been written.  m0 is reserved: the compiler keeps
+// nothing in it and sets it before each use of its own (there is none here), so
+// it is not among the clobbers, where it would only draw a warning.
 template <bool kNonTemporal>
 __device__ __forceinline__ void lm_lds_copy(u32x4 rsrc, int voff, int k0b, uint32_t lds) {
     if constexpr (kNonTemporal)
