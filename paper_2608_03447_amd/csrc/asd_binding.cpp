@@ -100,7 +100,7 @@ struct Shared {
             return false;
         void** const ptr[2] = {&accept, &next};
         for (int k = 0; k < 2; ++k) {
-            if (*ptr[k]) {
+            if (a[6 + k] != Py_None) {        // also an empty one, whose pointer is null
                 Py_INCREF(a[6 + k]);
                 outputs[k] = a[6 + k];
             } else {

@@ -108,6 +108,19 @@ def test_calls_run_without_a_binding(monkeypatch):
         assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("native", [True, False])
+@pytest.mark.parametrize("n", [0, 2])
+def test_given_outputs_are_the_ones_returned(n, native, monkeypatch):
+    monkeypatch.setattr(asd, "_fast", asd._load_fast() if native else _Declines())
+    s = _state(n=max(n, 1), k=1)
+    acc = torch.empty(n, dtype=torch.int32, device=DEV)
+    nxt = torch.empty(n, dtype=torch.int32, device=DEV)
+    rows = 2 * n
+    out = asd.asd_verify(s.logits[:rows], s.draft[:rows], s.lens[:n], s.tau[:n], s.cap[:n],
+                         s.budget[:n], out_accept_len=acc, out_next_token=nxt)
+    assert out[0] is acc and out[1] is nxt
+
+
 CHANGES = {
     "scalar controls": lambda s: setattr(s, "tau", 2.0) or setattr(s, "cap", 1),
     "strided drafts": lambda s: setattr(s, "draft", s.draft.repeat_interleave(2)[::2]),
