@@ -471,10 +471,10 @@ asd_status asd_read_probe(const void *buf, int64_t rows, int64_t row_bytes, uint
 /*
  * asd_mfma_probe -- a measurement helper: the matrix-core work of
  * asd_lmhead_verify with no memory traffic.  Each of `workgroups` workgroups
- * has the LM-head kernel's shape (eight wavefronts, each with 4 x 2 tiles of
- * 32 x 32 binary32 accumulators) and runs `steps` K steps of 64, i.e. 32
- * v_mfma_f32_32x32x16_bf16 per wavefront per step (2^23 flops per workgroup
- * per step), on operand fragments read once from `operands` and held in
+ * has the LM-head kernel's shape for tiles of 256 rows (eight wavefronts, each
+ * with 4 x 8 tiles of 16 x 16 binary32 accumulators) and runs `steps` K steps of
+ * 64, i.e. 64 v_mfma_f32_16x16x32_bf16 per wavefront per step (2^23 flops per
+ * workgroup per step), on operand fragments read once from `operands` and held in
  * registers.  The matrix cores' power depends on their operands, so the caller
  * passes data of the distribution it measures.  Run over an LM-head launch's
  * workgroups and steps (steps = d / 64), its duration is the practical

@@ -130,11 +130,11 @@ asd_status check_args(const void* logits, asd_dtype dtype, int64_t vocab, int32_
 }
 
 // The counter of the single-launch form for a call on stream `s`, or nullptr
-// for the two-launch form.  The smallest eager calls are bound by host launches,
-// so one launch wins (one request of 8 drafts 7.2 us a call, where two launches
-// cost the host 8.7); inside a captured graph launches cost little and the two
-// kernels are faster (7.2 against 7.7 us on the GPU), so a call being captured
-// takes two launches.
+// for the two-launch form.  The smallest eager calls of the Python binding are
+// bound by host launches, so one launch wins (one request of 8 drafts 7.3 us a
+// call, with two launches 8.5, all of it host time); inside a captured graph
+// launches cost little and the two kernels are faster (on the GPU 6.4 against
+// 7.3 us), so a call being captured takes two launches.
 unsigned* single_launch_counter(hipStream_t s, unsigned* counter) {
     if (counter == nullptr) return nullptr;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;

@@ -11,10 +11,11 @@
 // raises what it refuses.
 //
 // A call's checks, pointers and outputs in Python took more host time than the
-// GPU needs for a small round.  Host time per call, before and after: one
-// request with 8 drafts of 32,000 logits 15.5 and 5.7 us (the call itself 15.5
-// and 7.5 us, now the kernel's time); verify with commit 20.0 and 8.2 us; the
-// opportunity statistic 12.2 and 3.5 us; the fused output layer 21.9 and 10.5.
+// GPU needs for a small round.  Host time per call of the public functions, before
+// and after: one request with 8 drafts of 32,000 logits 15.5 and 5.8 us (3.8 of it
+// in this module and the launch; the call itself 15.5 and 7.3 us, now the
+// kernel's time); verify with commit 20.0 and 8.2 us; the opportunity statistic
+// 12.2 and 3.5 us; the fused output layer 21.9 and 10.5.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 

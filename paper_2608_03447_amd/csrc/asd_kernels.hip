@@ -1051,11 +1051,21 @@ __global__ __launch_bounds__(kScanThreads) void asd_scan_kernel(const ScanArgs A
 // runs Algorithm 1 for every request, one wavefront per request, writes the
 // argmax of split rows and resets the counter to zero for the next call.  No
 // tile waits for another.  The records and partials pass by the L2s (put and
-// get above), so the counter needs no release and no acquire, each of which
-// costs a pass over an L2: 9 rows of 32,000 f32 take 7.7 us on the GPU, 8.2
-// with them, and 270 tiles 11.3 for 14.3.  The counter must be zero when the
-// call starts: it lives in a header of the library's workspaces that is zeroed
-// when they are allocated, and every call leaves it at zero.
+// get above), so the counter takes no release and no acquire, each of which
+// costs a pass over an L2: 9 rows of 32,000 f32 7.7 us on the GPU, 8.2 with them,
+// and 270 tiles 11.3 for 14.3.  The counter must be zero when the call starts: it
+// lives in a header of the library's workspaces that is zeroed when they are
+// allocated, and every call leaves it at zero.
+//
+// In the language's terms the relaxed counter orders nothing.  The hand-over
+// relies on gfx950: an agent-scope store (sc1) is written through to the memory
+// that all XCDs share and leaves vmcnt when it has arrived there, so a writer
+// that waits for vmcnt(0) before it counts has published its output; an
+// agent-scope load (sc1) is not served from an L2's older copy; and the reader
+// issues its loads after the barrier that follows the counter's return.  These are
+// the steps by which the compiler itself makes an agent-scope release and acquire,
+// without the write-back and the invalidation, which only plain accesses need;
+// nothing but put's outputs passes between workgroups here.
 // Small plans have less than a tile per CU, so the kernel takes the registers
 // it needs (no occupancy bound).
 static_assert(kSingleLaunchMaxRequests <= 2 * kWaves, "two requests per wavefront at most");

@@ -96,13 +96,20 @@ Plan make_plan(int elem_bytes, int64_t vocab, int64_t rows, int32_t num_requests
 
 // Plans small enough for one launch (row pass and scan in one kernel; see
 // asd_row_scan_kernel): few tiles, and few requests, since the last tile scans
-// every request with its four wavefronts.  A second launch costs the host about
-// 2.4 us of 8.7; counting on one counter costs each tile of the single launch a
-// wait for its output and about 10 ns of the counter.  Time on the GPU, back to
-// back, one launch against two: 63 tiles 7.7 and 7.2 us, 75 tiles 8.8 and 8.5,
-// 270 tiles 11.3 and 9.1, 396 tiles 14.0 and 9.5, 720 tiles 20.1 and 10.4 (15 us
-// with the counter split over several lines of memory).  So up to 96 tiles the
-// saved launch is worth more, and two launches are faster above.
+// every request with its four wavefronts.  A second launch costs the host 2.8 us;
+// counting on one counter costs each tile a wait for its output and about 10 ns.
+// The limit lies where calls of the Python binding cross, which the host bounds
+// when they take two launches.  us a call, one launch against two, one box:
+//
+//   tiles               63 (9 rows of 32,000 f32)   91     96     104    120
+//   Python, in a row    7.3 / 8.5      7.6-8.1 / 8.4   8.0 / 8.4   8.0 / 8.4   8.5 / 8.4
+//   C, in a row         7.3 / 6.4      7.6-8.0 / 6.6   8.0 / 6.5   7.9 / 6.8   8.4 / 6.7
+//   one call alone      19.8 / 19.0    20.2 / 19.4     20.4 / 19.4   20.4 / 19.7   20.9 / 19.7
+//   host of the call    5.8 / 8.7
+//
+// (The Python figures are of the public functions; C stands for the entry point
+// called through the binding's native function.)  Single launches of more tiles
+// lose everywhere: 270 tiles 11.3 / 8.1 us, 720 tiles 20.1 / 10.4.
 constexpr int64_t kSingleLaunchMaxTiles = 96;
 constexpr int32_t kSingleLaunchMaxRequests = 8;   // two per wavefront of the last tile
 inline bool single_launch(const Plan& p) {
