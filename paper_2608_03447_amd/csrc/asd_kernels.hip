@@ -1390,8 +1390,8 @@ __global__ __launch_bounds__(kScanThreads) void asd_commit_kernel(
 // copies into the freed stage overlap the rest.
 //
 // What bounds large calls is the chip's power.  4,352 rows, 151,936 columns, d =
-// 5,120, Gaussian data: 4.53-4.56 ms (1,485-1,495 TFLOP/s) at 1.7 GHz with the
-// matrix cores 83% busy; on data of ones the kernel clocks 2.4 GHz.  So it is
+// 5,120, Gaussian data: 4.46-4.73 ms (1,430-1,520 TFLOP/s, by box) at 1.4-1.8 GHz
+// with the matrix cores 81-84% busy; on data of ones the kernel clocks 2.4 GHz.  So it is
 // built to spend little energy per flop: 16x16x32 MFMAs, which move half the
 // accumulator bytes of 32x32x16 (registers-only probe 1,955 against 1,725
 // TFLOP/s; this kernel's 32x32x16 predecessor took 5.08 ms on the same box),
@@ -1841,9 +1841,9 @@ __global__ __launch_bounds__(kLmThreads) void asd_lmhead_kernel(
 //    rows in different orders, so the greater of two duplicates was a matter of
 //    rounding.)
 //
-// 151,936 columns, d = 5,120, call times on one box against the tile kernels
-// that took these rows before: 9 rows 236 us (6.6 TB/s) against 425; 32 rows
-// 249 / 424; 64 rows 274 / 415; 128 rows 334 / 433.
+// 151,936 columns, d = 5,120, call times on one box against the tile kernel above
+// on the same rows: 9 rows 234 us (6.7 TB/s) against 302; 32 rows 232 / 303; 64
+// rows 252 / 309; 128 rows 313 / 326.
 //
 // Each K step waits until at most the copies of the later stages are outstanding
 // (they complete in order), then meets the other wavefronts: the step's stage is
