@@ -2265,9 +2265,10 @@ hipError_t launch_lmhead_verify(const void* hidden, const void* weight, int64_t 
         // The rows rounded up to a power of two of 16-row groups.  One group
         // leaves LDS for two workgroups per CU (with four waves); for eight
         // groups wide tiles read the hidden states less often (128 rows, d =
-        // 5,120: 334 us with 256 columns, 360 us with 128), but their ring is
-        // one stage shorter, which costs more where a CU has one narrow tile
-        // only (vocabulary 32,000, d = 1,024: 36.2 against 33.5 us).
+        // 5,120: 316 us with 256 columns, 323-328 us with 128), but their ring
+        // is one stage shorter, which costs more where a CU has one narrow tile
+        // only (128 rows, vocabulary 32,000: d = 1,024, 30.1 against 27.5 us; d =
+        // 4,096, 78.8 against 65.8).
         auto launch = rows <= 16   ? launch_lmhead_stream<4, 1, 1, 128, 3>
                       : rows <= 32 ? launch_lmhead_stream<8, 1, 2, 128, 3>
                       : rows <= 64 ? launch_lmhead_stream<8, 1, 4, 128, 3>
